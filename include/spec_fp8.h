@@ -196,12 +196,18 @@ spec_status spec_fp8_kv_cache_write(const void* k, int64_t ld_k, const void* v, 
  * Y       bf16 or fp32 [M, ldy], N <= ldy.
  * workspace  device scratch of at least spec_fp8_gemm_workspace_bytes(M,N,K)
  *         bytes (may be NULL when that is 0), 16-byte aligned.  Where the
- *         K dimension is split over workgroups, its first 16 KiB hold one
- *         ticket per output tile: they must be zero before the first call that
+ *         K dimension is split over workgroups, its first 16 KiB hold
+ *         tickets: they must be zero before the first call that
  *         uses the workspace (fill it with zeros once, e.g. when allocating),
  *         and every call leaves them zero again, so one workspace serves every
  *         later call of any shape.  The rest of it is overwritten.  Calls that
  *         share a workspace must not overlap (one stream, or serialized).
+ *         It is required (SPEC_ERR_WORKSPACE, SPEC_ERR_ALIGN otherwise) for
+ *         the decode-sized projections: N < 12288 and either M <= 80, K >= 2048
+ *         and ceil(M/64)*ceil(N/64) <= 128, or 80 < M <= 320, K >= 256 and
+ *         (N <= 4096 or K >= 2N).  For other shapes with a nonzero size a call
+ *         without a usable workspace runs with K unsplit (slower, and its fp32
+ *         summation order differs).
  * Requirements: M >= 0 (0 is a no-op), N > 0, K > 0, K % 128 == 0 (else
  * SPEC_ERR_UNSUPPORTED); lda % 16 == 0, ldw % 16 == 0, A and W 16-byte
  * aligned; ldy % 8 == 0 and Y 16-byte aligned.  M and N need not be tile

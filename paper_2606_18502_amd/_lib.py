@@ -11,6 +11,7 @@ LIB_PATH = os.path.join(_HERE, "libspecfp8.so")
 # enums and limits (include/spec_fp8.h)
 ACCEPT_SCRATCH_BYTES = 16 << 20
 SPEC_OK = 0
+ERR_WORKSPACE = 6
 STATUS_NAMES = {0: "SPEC_OK", 1: "SPEC_ERR_NULL", 2: "SPEC_ERR_SHAPE", 3: "SPEC_ERR_UNSUPPORTED",
                 4: "SPEC_ERR_ENUM", 5: "SPEC_ERR_ALIGN", 6: "SPEC_ERR_WORKSPACE", 7: "SPEC_ERR_HIP",
                 8: "SPEC_ERR_VALUE", 9: "SPEC_ERR_SCRATCH"}

@@ -25,7 +25,9 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libspecfp8.so")
 ARCH = "gfx950"
 
-HIP_SOURCES = ["quantize.hip", "kvcache.hip", "gemm.hip", "accept.hip", "tree_mask.hip", "api.cpp", "plan.cpp"]
+# longest compiles first: they run in parallel
+HIP_SOURCES = ["gemm_k0_1.hip", "gemm_k2_3.hip", "gemm_k4_6.hip", "gemm_k7_12.hip", "accept.hip", "quantize.hip",
+               "gemm.hip", "kvcache.hip", "tree_mask.hip", "api.cpp", "plan.cpp"]
 HOST_SOURCES = ["validate.cpp"]
 
 

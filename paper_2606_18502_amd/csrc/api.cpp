@@ -5,6 +5,7 @@
 
 #include "../../include/spec_fp8.h"
 #include "kernels.hpp"
+#include "plan.hpp"
 #include "validate.hpp"
 
 namespace {
@@ -78,11 +79,15 @@ spec_status spec_fp8_gemm(const uint8_t* a, int64_t lda, const float* a_scale, s
     const spec_status st = specfp8::check_gemm(a, lda, a_scale, (int)a_mode, w, ldw, w_scale, (int)w_mode, M, N, K,
                                                y, ldy, (int)out_dtype);
     if (st != SPEC_OK || M == 0) return st;
-    const specfp8::GemmPlan plan = specfp8::plan_gemm(M, N, K);
+    specfp8::GemmPlan plan = specfp8::plan_gemm(M, N, K);
     if (!grid_fits(plan)) return SPEC_ERR_UNSUPPORTED;
     if (plan.workspace_bytes > 0) {
-        if (!workspace || workspace_bytes < plan.workspace_bytes) return SPEC_ERR_WORKSPACE;
-        if ((reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return SPEC_ERR_ALIGN;
+        const bool enough = workspace && workspace_bytes >= plan.workspace_bytes;
+        const bool aligned = (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+        if (!enough || !aligned) {
+            if (specfp8::gemm_workspace_required(M, N, K)) return enough ? SPEC_ERR_ALIGN : SPEC_ERR_WORKSPACE;
+            plan = specfp8::plan_gemm(M, N, K, specfp8::kEpiPlain, false);   // no usable workspace: K is not split
+        }
     }
     return from_hip(specfp8::launch_gemm(plan, a, lda, a_scale, a_mode == SPEC_SCALE_PER_TENSOR, w, ldw, w_scale,
                                          w_mode == SPEC_SCALE_PER_TENSOR, M, N, K, y, ldy, out_dtype == SPEC_OUT_F32,
@@ -105,7 +110,9 @@ spec_status spec_fp8_gemm_logit_stats(const uint8_t* a, int64_t lda, const float
     const specfp8::GemmPlan plan = specfp8::plan_gemm(M > 0 ? M : 1, V, K, specfp8::kEpiStats);
     st = specfp8::check_logit_stats(M, V, temperature, logits, ld_logits, stats, ld_stats, plan.stat_groups);
     if (st != SPEC_OK || M == 0) return st;
-    if (!grid_fits(plan) || !specfp8::gemm_strides_fit(plan.kind, lda, ldw)) return SPEC_ERR_UNSUPPORTED;
+    // the wide LM-head tile takes no longer strides than its 32-bit offsets reach
+    if (!grid_fits(plan) || (plan.kind == specfp8::kLmHeadKind && !specfp8::gemm_strides_fit(plan.kind, lda, ldw)))
+        return SPEC_ERR_UNSUPPORTED;
     const float c2 = temperature > 0.0f ? (float)(1.4426950408889634 / (double)temperature) : 0.0f;
     return from_hip(specfp8::launch_gemm(plan, a, lda, a_scale, a_mode == SPEC_SCALE_PER_TENSOR, w, ldw, w_scale,
                                          w_mode == SPEC_SCALE_PER_TENSOR, M, V, K, logits, ld_logits, 0, nullptr,

@@ -21,6 +21,15 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
     return u >> 16;
 }
 
+// Two fp32 values -> two bf16 bit patterns (a in the low half) with the
+// hardware conversion: round to nearest even, as f32_to_bf16_rne.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f32_to_bf16x2(float a, float b) {
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
 // The SiLU gate of the FFN (shared by the SiLU-gated quantize and the GEMM
 // epilogue that fuses it, so both give the same h for the same g, u):
 // h = bf16(silu(g) * u) with silu(g) = g / (1 + e^-g) = g * rcp(1 + 2^(-g log2 e)),

@@ -30,7 +30,6 @@ struct GemmPlan {
     int kind;              // tile configuration (plan.hpp, kTiles)
     int m_tiles, n_tiles;  // output tiles
     int splits;            // K-splits (1 = none)
-    int reduce;            // kReduceLast when K is split (plan.hpp, GemmReduce)
     int group_m;           // > 1: tile order in groups of group_m M-tiles
     int krot_on;           // staggered K start per N-tile
     int64_t stat_groups;   // column groups per row of the epilogue statistics (n_tiles * waves across N)
@@ -40,14 +39,17 @@ struct GemmPlan {
 // Epilogue of a plan: plain (K may be split), logit statistics, or the
 // SiLU-gated output; the last two keep one workgroup per output tile.
 enum GemmEpilogue { kEpiPlain = 0, kEpiStats = 1, kEpiSilu = 2 };
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue = kEpiPlain);
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue = kEpiPlain, bool may_split = true);
+// Decode-sized projections, for which the caller has to bring a workspace even
+// where the plan would do without; elsewhere K is split only if there is one.
+bool gemm_workspace_required(int64_t M, int64_t N, int64_t K);
 // The plan for an explicit tile kind and K split (plan_gemm's choices are
 // made through it; also used to compare configurations).
 GemmPlan plan_gemm_as(int64_t M, int64_t N, int64_t K, int kind, int splits, int epilogue = kEpiPlain);
-// Whether the kernel of tile kind `kind` can address operands with these row
-// strides: the in-place-refill kernels need a tile's rows of A and of W to
-// span at most 4 GiB ((BM - 1) lda + 128 and (BN - 1) ldw + 128 <= 2^32);
-// the others take any stride.
+// Whether the kernels of tile kind `kind` can address operands with these row
+// strides: a tile's rows of A and of W must each span at most 4 GiB ((BM - 1)
+// lda + 128 and (BN - 1) ldw + 128 <= 2^32).  launch_gemm takes a slower kernel
+// for longer strides.
 bool gemm_strides_fit(int kind, int64_t lda, int64_t ldw);
 // stats_mode 0: plain GEMM; 1/2: also the per-(row, column group) statistics
 // of the bf16 output (softmax in base 2 with c2 = log2(e)/T, or argmax) into

@@ -11,53 +11,85 @@ namespace {
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// A CU's operand rows per K-step over the whole GEMM: the rounds of tiles the
-// 256 CUs run, times a tile's rows (BM + BN).  A CU streams its operand bytes
-// at a rate no tile shape changes, so this orders tile shapes by time.
-int64_t rows_per_cu(int64_t M, int64_t N, int kind) {
+// Estimated time (us, up to a constant) of an M x N x K GEMM on tile kind
+// `kind` with K split `splits` ways: the K-steps of the busiest compute unit
+// (its workgroups share it, or follow each other where LDS holds no more), a
+// fixed cost per workgroup batch and its epilogue, the operand and output
+// bytes, and the split-K reduction.  The constants are a fit to 11,000 timings
+// (MI355X, cold weights: 16 shapes N x K from 768 x 4096 and 4096 x 512 to
+// 28672 x 4096 and 4096 x 14336 at 32 values of M from 1 to 4096, every kind,
+// splits 1 to 12); over the 510 shapes the kind and split it picks take 0.9%
+// longer than the fastest measured (10% of them more than 3.5%, at most 24%:
+// K of 4 steps), and none longer than the rules by ranges of M it replaced
+// (1.56 times as long on average).
+double estimate_us(int64_t M, int64_t N, int64_t K, int kind, int splits) {
+    const TileShape& t = kTiles[kind];
     const int64_t tiles = ((M + tile_bm(kind) - 1) / tile_bm(kind)) * ((N + tile_bn(kind) - 1) / tile_bn(kind));
-    return ((tiles + 255) / 256) * (int64_t)(tile_bm(kind) + tile_bn(kind));
+    const int64_t per_cu = (tiles * splits + 255) / 256;         // workgroups of the busiest of 256 compute units
+    const int64_t steps = (K / kGemmBK + splits - 1) / splits;
+    const int64_t resident = 160 / t.lds;
+    const double batches = (double)((per_cu + resident - 1) / resident);
+    const double blocks = t.wtm * t.wtn;                           // 16x16 blocks per wave
+    double us = t.step_us * (double)per_cu * (double)steps + batches * (1.61 + 0.102 * blocks) +
+                ((double)N * (double)K + (double)M * (double)K) / 10.1e6 + 0.119e-6 * 2.0 * (double)M * (double)N;
+    if (splits > 1) us += 0.7 + splits * (0.3 + 0.062 * blocks);
+    return us;
 }
+
+// The kind and split with the smallest estimate among those that have the
+// epilogue.  A split keeps at least 3 K-steps per workgroup and at most 640
+// workgroups (beyond both, partial tiles outweigh the gain).
+GemmPlan best_plan(int64_t M, int64_t N, int64_t K, int epilogue, bool may_split) {
+    const int need = epilogue == kEpiStats ? kHasStats : (epilogue == kEpiSilu ? kHasSilu : 0);
+    const int64_t ksteps = K / kGemmBK;
+    int kind = kFarKind, splits = 1;
+    double best = -1.0;
+    for (int k = 0; k < kTileKinds; ++k) {
+        if ((kTiles[k].has & need) != need) continue;
+        const int64_t tiles = ((M + tile_bm(k) - 1) / tile_bm(k)) * ((N + tile_bn(k) - 1) / tile_bn(k));
+        const bool can = may_split && epilogue == kEpiPlain && (kTiles[k].has & kHasSplit) != 0;
+        for (int s = 1; s <= (can ? 8 : 1); ++s) {
+            if (s > 1 && (ksteps / s < 3 || tiles * s > 640)) break;
+            const double us = estimate_us(M, N, K, k, s);
+            if (best < 0.0 || us < best) {
+                best = us;
+                kind = k;
+                splits = s;
+            }
+        }
+    }
+    return plan_gemm_as(M, N, K, kind, splits, epilogue);
+}
+
+// A staggered K start pays where few M-tiles read many N-tiles of weights in
+// step: their row stride puts one K column of all rows on few memory channels
+// (N = 28672, K = 4096: M = 8 24.0 -> 22.4 us, M = 80 28.4 -> 27.3 us; equal
+// from N = 6144 down, where the tiles are few).
+bool stagger_pays(const GemmPlan& p) { return p.splits == 1 && p.m_tiles <= 2 && p.n_tiles >= 192; }
 
 }  // namespace
 
 GemmPlan plan_gemm_as(int64_t M, int64_t N, int64_t K, int kind, int splits, int epilogue) {
     GemmPlan p{};
-    if (kind < 0 || kind >= kTileKinds) kind = 2;
-    // the statistics epilogues never split K; the 160x224 tile has no
-    // statistics variant (it would spill), 160x192 takes its place
-    if (epilogue == kEpiStats && kind == 2) kind = 4;
-    // the in-place-refill kernels have the plain epilogue only (kRollStatsKind
-    // also the statistics one) and no K split
-    if (kTiles[kind].roll && epilogue != kEpiPlain && !(epilogue == kEpiStats && kind == kRollStatsKind))
-        kind = epilogue == kEpiStats ? 4 : 2;
-    if (kTiles[kind].roll) splits = 1;
-    if (epilogue != kEpiPlain) splits = 1;
+    if (kind < 0 || kind >= kTileKinds) kind = kFarKind;
     p.kind = kind;
     const int bm = tile_bm(kind), bn = tile_bn(kind);
     p.m_tiles = (int)((M + bm - 1) / bm);
     p.n_tiles = (int)((N + bn - 1) / bn);
     const int64_t tiles = (int64_t)p.m_tiles * p.n_tiles;
-    // the 160x224 kernel has no in-kernel reduction (its registers are
-    // full), and a tile without a ticket cannot be reduced: no K split
-    if (kind == 2 || tiles > (int64_t)(kGemmTicketBytes / sizeof(unsigned int))) splits = 1;
     const int ksteps = (int)(K / kGemmBK);
+    // only the plain epilogue of some kinds splits K, and only with a ticket per tile and wave
+    if (epilogue != kEpiPlain || !(kTiles[kind].has & kHasSplit) ||
+        tiles * tile_waves(kind) > (int64_t)(kGemmTicketBytes / sizeof(unsigned int)))
+        splits = 1;
     if (splits > ksteps) splits = ksteps;
     if (splits < 1) splits = 1;
-    // every split must own at least one K-step after ceil division
-    while (splits > 1 && (int64_t)((ksteps + splits - 1) / splits) * (splits - 1) >= ksteps) --splits;
     p.splits = splits;
-    p.reduce = splits > 1 ? kReduceLast : kReduceNone;
-    // Many M-tiles (long prompts): tiles in groups of 4 M-tiles with K walked
-    // in step, so the 32 tiles an XCD runs at once re-read 4 activation and
-    // 8 weight tiles from its L2 (5-8% at M = 4096).  Few M-tiles keep the
-    // staggered K start, which spreads the requests for shared rows.
-    p.group_m = 1;
-    p.krot_on = 1;
-    if (p.m_tiles >= 8 && splits == 1) {
-        p.group_m = 4;
-        p.krot_on = 0;
-    }
+    // Many M-tiles (long prompts): tiles in groups of 4 M-tiles, so the 32
+    // tiles an XCD runs at once re-read 4 activation and 8 weight tiles from
+    // its L2 (5-8% at M = 4096).
+    p.group_m = p.m_tiles >= 8 && splits == 1 ? 4 : 1;
+    p.krot_on = 0;
     p.stat_groups = (int64_t)p.n_tiles * kTiles[kind].wn;
     p.part_off = kGemmTicketBytes;
     p.workspace_bytes =
@@ -66,80 +98,31 @@ GemmPlan plan_gemm_as(int64_t M, int64_t N, int64_t K, int kind, int splits, int
 }
 
 bool gemm_strides_fit(int kind, int64_t lda, int64_t ldw) {
-    if (kind < 0 || kind >= kTileKinds || !kTiles[kind].roll) return true;
+    if (kind < 0 || kind >= kTileKinds) return true;
     const uint64_t lim = 1ull << 32;
     return (uint64_t)(tile_bm(kind) - 1) * (uint64_t)lda + kGemmBK <= lim &&
            (uint64_t)(tile_bn(kind) - 1) * (uint64_t)ldw + kGemmBK <= lim;
 }
 
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue) {
-    const int ksteps = (int)(K / kGemmBK);
-    int splits = 1;
-    // Tile shapes by measurement on MI355X (M = B*(k+1) verify rows).
-    if (M <= 80) {
-        // Draft and small verify batches: a weight stream with a fixed cost
-        // per workgroup.  Very wide N (gate|up) fills the chip unsplit;
-        // otherwise 64x64 tiles with K split until about 256 workgroups run
-        // (one round of the CUs: at M = 80 the long-K down projection took
-        // 25.2 us split in 4, 512 workgroups, and 23.6 us split in 2),
-        // keeping >= 8 K-steps per split.  The last workgroup of a tile adds
-        // its partial tiles: one launch fewer, 1-2 us per GEMM here.
-        if (N >= 192 * 64) return plan_gemm_as(M, N, K, M <= 64 ? 8 : 1, 1, epilogue);
-        const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-        splits = (int)(256 / tiles);
-        const int max_split = ksteps / 8 > 0 ? ksteps / 8 : 1;
-        if (splits > max_split) splits = max_split;
-        if (splits > 16) splits = 16;
-        return plan_gemm_as(M, N, K, 0, splits, epilogue);
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue, bool may_split) {
+    GemmPlan p = best_plan(M, N, K, epilogue, may_split);
+    // The logits stored with their statistics are the unsplit plain GEMM's bit
+    // for bit: both walk K in the same order, so K starts are staggered only
+    // where both take the same tile.
+    if (stagger_pays(p)) {
+        if (epilogue == kEpiSilu) p.krot_on = 1;
+        else p.krot_on = best_plan(M, N, K, epilogue == kEpiPlain ? kEpiStats : kEpiPlain, may_split).kind == p.kind;
     }
-    if (M <= 320) {
-        // wide N: one 160x224 tile per CU (gate|up), or 160x192 for an LM
-        // head (160x224 with a ragged last tile where N % 192 != 0); where the
-        // tiles take several rounds of the CUs (an LM head), the 160x384
-        // in-place-refill tile streams fewer operand rows per CU
-        if (N % 224 == 0 && N >= 224 * 64 && rows_per_cu(M, N, 2) <= rows_per_cu(M, N, 11))
-            return plan_gemm_as(M, N, K, 2, 1, epilogue);
-        if (N >= 192 * 64) {
-            // the plain epilogue takes the fewest rows per CU among 160x192
-            // (160x224 where it divides N better), 160x224 and 160x384; the
-            // statistics epilogue takes the same tile where it has one
-            // (160x384), else 160x192 (160x224 where it divides N better)
-            int stats_kind = (N % 192 == 0) ? 4 : 2;
-            int plain_kind = stats_kind;
-            if (rows_per_cu(M, N, 2) < rows_per_cu(M, N, plain_kind)) plain_kind = 2;
-            if (ksteps >= 2 && ksteps % 2 == 0 && rows_per_cu(M, N, 11) < rows_per_cu(M, N, plain_kind))
-                plain_kind = 11;
-            if (plain_kind == kRollStatsKind) stats_kind = kRollStatsKind;
-            GemmPlan p = plan_gemm_as(M, N, K, epilogue == kEpiPlain ? plain_kind : stats_kind, 1, epilogue);
-            // Both walk K in order, so that the logits stored with their
-            // statistics are the plain GEMM's bit for bit also where the two
-            // take different tiles (a staggered K start gained nothing
-            // measurable on the LM head).
-            if (plain_kind != stats_kind || plain_kind == kRollStatsKind) p.krot_on = 0;
-            return p;
-        }
-        // Short N (QKV, O, down).  A CU streams its operand rows at a rate
-        // that no tile shape or wave count tried raised (~35 GB/s per CU at
-        // every shape of the verify step), so a CU's time follows the operand
-        // bytes it streams; a K split pays when it brings idle CUs in, and its
-        // partial tiles are added by the last workgroup of each tile.  Sweeps
-        // (cold weights) chose: long K (down, 14336 -> 4096) 80x128 tiles with
-        // K split in 2; N <= 4096 (O) 160x64 split in 2; else (QKV) 64x128
-        // unsplit.
-        if (K >= 2 * N) return plan_gemm_as(M, N, K, 1, 2, epilogue);
-        if (N <= 4096) return plan_gemm_as(M, N, K, 7, 2, epilogue);
-        return plan_gemm_as(M, N, K, 8, 1, epilogue);
-    }
-    // Long prompts.  A CU's time is its operand bytes: per tile (BM + BN)
-    // rows per K-step, times the rounds of tiles every CU runs.  The 256-wide
-    // in-place-refill tiles stream fewer rows per output; take the kind with
-    // the fewest rows per CU (an even number of K-steps is required by them).
-    int best = 2;
-    if (M >= 1024 && epilogue == kEpiPlain && ksteps >= 2 && ksteps % 2 == 0) {
-        for (int kind : {9, 10})
-            if (rows_per_cu(M, N, kind) < rows_per_cu(M, N, best)) best = kind;
-    }
-    return plan_gemm_as(M, N, K, best, 1, epilogue);
+    if (epilogue == kEpiPlain && p.workspace_bytes == 0 && gemm_workspace_required(M, N, K))
+        p.workspace_bytes = kGemmTicketBytes;
+    return p;
+}
+
+bool gemm_workspace_required(int64_t M, int64_t N, int64_t K) {
+    const int64_t ksteps = K / kGemmBK;
+    if (N >= 192 * 64 || M > 320) return false;
+    if (M <= 80) return ksteps >= 16 && 2 * ((M + 63) / 64) * ((N + 63) / 64) <= 256;
+    return ksteps >= 2 && (K >= 2 * N || N <= 4096);
 }
 
 AcceptPlan plan_accept(int64_t B, int64_t k, int64_t V) {

@@ -9,64 +9,67 @@ namespace specfp8 {
 
 // ---- FP8 GEMM tiles ---------------------------------------------------------
 // A tile is a WM x WN grid of waves, each wave holding WTM x WTN blocks of
-// 16x16 outputs; STAGES LDS buffers rotate through the K-loop (deeper
-// pipelines, 6 stages of 64x128 or 8 of 64x64, measured no faster).  roll: the
-// kernel whose operand fragments are refilled in place (one fragment set;
-// never split in K; plain epilogue only, but for kRollStatsKind, which also
-// has the statistics epilogue).  rspan8, lspan8: the K-step schedule of the
-// non-roll kernel, numerators over 8 of the step's MFMAs: the next step's LDS
-// operand reads go out over the first rspan8/8 of them and the stage refill
-// loads over the first lspan8/8 (chosen by cold same-run sweeps: spreading the
-// refills over the whole step took down at M = 320 from 45.8 to 42.8 us and
-// gate|up from 48.3 to 46.7 us; the short-N tiles measured best at 5/8, 4/8).
+// 16x16 outputs; STAGES LDS buffers rotate through the K-loop.  lspan8: a
+// K-step's stage loads go out over the first lspan8/8 of its MFMAs.  t1 > 0:
+// the alternating schedule of the large tiles, whose stage is free before MFMA
+// t1; late8: with two stages, the next step's stage has to have landed before
+// MFMA late8/8 of the step.  staged: the plain bf16 output leaves through LDS
+// (statistics epilogues always do).  has: the kernels a kind has beside the
+// plain one (each is compiled separately).  step_us: the time of one K-step of
+// a workgroup alone on a compute unit, and lds the KiB it holds, for the
+// planner's estimate (plan.cpp).
 struct TileShape {
-    int wtm, wtn, wm, wn, stages, roll, rspan8, lspan8;
+    int wtm, wtn, wm, wn, stages, lspan8, late8, t1, staged, has;
+    double step_us;
+    int lds;
 };
+constexpr int kHasSplit = 1, kHasStats = 2, kHasSilu = 4;
 
-// kind  BM x BN   waves (wave tile)     stages  LDS      used for
-//  0    64 x 64   2x2 (32x32)           4       64 KiB   M <= 80 (K split)
-//  1    80 x 128  1x2 (80x64)           4       104 KiB  M <= 80 wide N; M <= 320 long K (split)
-//  2   160 x 224  2x2 (80x112)          3       144 KiB  M <= 320 wide N, large M
-//  3   256 x 128  2x2 (128x64)          3       144 KiB
-//  4   160 x 192  2x2 (80x96)           3       132 KiB  wide N with statistics
-//  5   160 x 128  2x2 (80x64)           4       144 KiB
-//  6   320 x 64   4x1 (80x64)           3       144 KiB
-//  7   160 x 64   2x2 (80x32)           4       112 KiB  M <= 320, N <= 4096 (split)
-//  8    64 x 128  2x2 (32x64)           4        96 KiB  M <= 64 wide N; M <= 320 short N
-//  9   256 x 224  2x2 (128x112), roll   2       120 KiB  large M
-// 10   256 x 256  2x2 (128x128), roll   2       128 KiB  large M
-// 11   160 x 384  2x2 (80x192), roll    2       136 KiB  M <= 320, very wide N (LM head, with statistics)
+// kind  BM x BN   waves (wave tile)  stages   chosen for
+//  0   256 x 256  2x2 (128x128)      2        large M
+//  1   160 x 384  2x2 (80x192)       2        M <= 320 and a very wide N (LM head)
+//  2   160 x 224  2x2 (80x112)       3        wide N
+//  3   128 x 256  2x2 (64x128)       3        wide N, large M
+//  4   256 x 128  2x2 (128x64)       3        large M, short N
+//  5   160 x 128  2x2 (80x64)        4        M from about 320 on
+//  6   128 x 128  2x2 (64x64)        4
+//  7   160 x 64   2x2 (80x32)        4        kinds 7 .. 12: small M or short N
+//  8    64 x 128  2x2 (32x64)        4
+//  9    80 x 128  1x4 (80x32)        3
+// 10    80 x 64   1x4 (80x16)        4
+// 11    64 x 64   2x2 (32x32)        4
+// 12    32 x 64   1x4 (32x16)        4        (a 16 x 64 tile was no faster at any M)
 constexpr TileShape kTiles[] = {
-    {2, 2, 2, 2, 4, 0, 5, 4}, {5, 4, 1, 2, 4, 0, 6, 8}, {5, 7, 2, 2, 3, 0, 6, 8}, {8, 4, 2, 2, 3, 0, 5, 4},
-    {5, 6, 2, 2, 3, 0, 5, 4}, {5, 4, 2, 2, 4, 0, 5, 4}, {5, 4, 4, 1, 3, 0, 5, 4}, {5, 2, 2, 2, 4, 0, 5, 4},
-    {2, 4, 2, 2, 4, 0, 5, 4}, {8, 7, 2, 2, 2, 1, 5, 4}, {8, 8, 2, 2, 2, 1, 5, 4}, {5, 12, 2, 2, 2, 1, 5, 4},
+    {8, 8, 2, 2, 2, 6, 3, 5, 1, kHasStats, 0.991, 134},
+    {5, 12, 2, 2, 2, 6, 3, 4, 1, kHasStats, 1.034, 139},
+    {5, 7, 2, 2, 3, 6, 0, 3, 1, kHasSilu, 0.643, 146},
+    {4, 8, 2, 2, 3, 6, 0, 3, 1, kHasSplit | kHasStats | kHasSilu, 0.668, 146},
+    {8, 4, 2, 2, 3, 6, 0, 3, 0, kHasSplit, 0.659, 146},
+    {5, 4, 2, 2, 4, 6, 0, 3, 0, kHasSplit, 0.479, 146},
+    {4, 4, 2, 2, 4, 6, 0, 3, 0, kHasSplit | kHasStats | kHasSilu, 0.433, 129},
+    {5, 2, 2, 2, 4, 8, 0, 0, 0, kHasSplit, 0.362, 113},
+    {2, 4, 2, 2, 4, 8, 0, 0, 0, kHasSplit | kHasStats | kHasSilu, 0.319, 97},
+    {5, 2, 1, 4, 3, 8, 0, 0, 0, kHasSplit | kHasSilu, 0.390, 79},
+    {5, 1, 1, 4, 4, 8, 0, 0, 0, kHasSplit, 0.261, 73},
+    {2, 2, 2, 2, 4, 8, 0, 0, 0, kHasSplit | kHasSilu, 0.207, 65},
+    {2, 1, 1, 4, 4, 8, 0, 0, 0, kHasSplit, 0.169, 49},
 };
 constexpr int kTileKinds = sizeof(kTiles) / sizeof(kTiles[0]);
-// The in-place-refill tile that also has the statistics epilogue (LM head).
-constexpr int kRollStatsKind = 11;
+constexpr int kLmHeadKind = 1;
+constexpr int kFarKind = 11;            // the kind that also has kernels with 64-bit operand offsets
 constexpr int tile_bm(int k) { return 16 * kTiles[k].wtm * kTiles[k].wm; }
 constexpr int tile_bn(int k) { return 16 * kTiles[k].wtn * kTiles[k].wn; }
-constexpr int tile_threads(int k) { return 64 * kTiles[k].wm * kTiles[k].wn; }
-// The non-roll kind with this wave grid and pipeline depth, or -1.
-constexpr int tile_kind_of(int wtm, int wtn, int wm, int wn, int stages) {
-    for (int k = 0; k < kTileKinds; ++k)
-        if (!kTiles[k].roll && kTiles[k].wtm == wtm && kTiles[k].wtn == wtn && kTiles[k].wm == wm &&
-            kTiles[k].wn == wn && kTiles[k].stages == stages)
-            return k;
-    return -1;
-}
+constexpr int tile_waves(int k) { return kTiles[k].wm * kTiles[k].wn; }
 
 constexpr int kGemmBK = 128;   // bytes (= E4M3 elements) of K per step
 
-// Split-K reduction: every workgroup of a split tile stores its partial tile
-// in the workspace, and the last of them to arrive (an atomic ticket per
-// tile) adds all of them in split order and writes the output.  The tickets
-// live in the first kGemmTicketBytes of the workspace, which must be zero
-// before the first call and which every call leaves zero again.  Plans with
-// more tiles than tickets, and the 160x224 tile (no registers left for the
-// reduction), do not split K.
-enum GemmReduce { kReduceNone = 0, kReduceLast = 1 };
-constexpr size_t kGemmTicketBytes = 16384;   // 4096 tile tickets
+// Split-K reduction: every wave of a split tile stores its part of the partial
+// tile in the workspace, and the last of the waves that hold the same part (an
+// atomic ticket per tile and wave) adds all of them in split order and writes
+// the output.  The tickets live in the first kGemmTicketBytes of the
+// workspace, which must be zero before the first call and which every call
+// leaves zero again.  Plans with more tiles than tickets do not split K.
+constexpr size_t kGemmTicketBytes = 16384;   // 4096 tickets
 
 // ---- acceptance ---------------------------------------------------------------
 constexpr int kAcceptThreads = 256;

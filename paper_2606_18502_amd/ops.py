@@ -201,16 +201,17 @@ def gemm(a: torch.Tensor, sa: torch.Tensor, w: torch.Tensor, sw: torch.Tensor,
         raise ValueError("out must be bf16 or fp32")
     _dev(out, out.dtype, "out")
     odt = _lib.OUT_F32 if out.dtype == torch.float32 else _lib.OUT_BF16
-    need = gemm_workspace_bytes(M, N, K)
+    args = (a.data_ptr(), _rowmajor(a, "a"), sa.data_ptr(), a_mode, w.data_ptr(), _rowmajor(w, "w"), sw.data_ptr(),
+            w_mode, M, N, K, out.data_ptr(), _rowmajor(out, "out"), odt)
     ws_ptr, ws_bytes = None, 0
-    if need:
-        if workspace is None or workspace.numel() * workspace.element_size() < need:
-            workspace = torch.zeros((need,), dtype=torch.uint8, device=a.device)   # tickets start at zero
+    if workspace is not None:
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    check("spec_fp8_gemm", lib.spec_fp8_gemm(a.data_ptr(), _rowmajor(a, "a"), sa.data_ptr(), a_mode,
-                                             w.data_ptr(), _rowmajor(w, "w"), sw.data_ptr(), w_mode, M, N, K,
-                                             out.data_ptr(), _rowmajor(out, "out"), odt, ws_ptr, ws_bytes,
-                                             _stream()))
+    status = lib.spec_fp8_gemm(*args, ws_ptr, ws_bytes, _stream())
+    if status == _lib.ERR_WORKSPACE:
+        # the shape needs a workspace and none large enough was given (tickets start at zero)
+        workspace = torch.zeros((gemm_workspace_bytes(M, N, K),), dtype=torch.uint8, device=a.device)
+        status = lib.spec_fp8_gemm(*args, workspace.data_ptr(), workspace.numel(), _stream())
+    check("spec_fp8_gemm", status)
     return out
 
 
