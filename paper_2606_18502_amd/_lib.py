@@ -11,7 +11,6 @@ LIB_PATH = os.path.join(_HERE, "libspecfp8.so")
 # enums and limits (include/spec_fp8.h)
 ACCEPT_SCRATCH_BYTES = 16 << 20
 SPEC_OK = 0
-ERR_WORKSPACE = 6
 STATUS_NAMES = {0: "SPEC_OK", 1: "SPEC_ERR_NULL", 2: "SPEC_ERR_SHAPE", 3: "SPEC_ERR_UNSUPPORTED",
                 4: "SPEC_ERR_ENUM", 5: "SPEC_ERR_ALIGN", 6: "SPEC_ERR_WORKSPACE", 7: "SPEC_ERR_HIP",
                 8: "SPEC_ERR_VALUE", 9: "SPEC_ERR_SCRATCH"}
@@ -94,7 +93,3 @@ def declare(lib: ctypes.CDLL) -> ctypes.CDLL:
     lib.spec_version.restype = i32
     return lib
 
-
-def check(fn: str, status: int) -> None:
-    if status != SPEC_OK:
-        raise SpecError(fn, status)

@@ -1,4 +1,4 @@
-"""Build libspecfp8.so (HIP for gfx950) in-tree.
+"""Build libspecfp8.so (HIP for gfx950) and its torch binding in-tree.
 
     python -m paper_2606_18502_amd.build [-v]
 
@@ -6,7 +6,9 @@ Every HIP source is compiled with hipcc for gfx950 only, without packed-fp32
 instructions (-packed-fp32-ops) and without floating-point contraction
 (-ffp-contract=off keeps the documented rounding of every scale, exp and
 epilogue step); the host-only validation unit is plain C++.  The objects are
-linked into paper_2606_18502_amd/libspecfp8.so, next to this file.
+linked into paper_2606_18502_amd/libspecfp8.so, next to this file, and the
+torch-facing argument marshalling (torch_bind.cpp, against the installed torch)
+into _torch_bind.so beside it.
 """
 
 from __future__ import annotations
@@ -17,6 +19,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -29,6 +32,8 @@ ARCH = "gfx950"
 HIP_SOURCES = ["gemm_k0_1.hip", "gemm_k2_3.hip", "gemm_k4_6.hip", "gemm_k7_12.hip", "accept.hip", "quantize.hip",
                "gemm.hip", "kvcache.hip", "tree_mask.hip", "api.cpp", "plan.cpp"]
 HOST_SOURCES = ["validate.cpp"]
+BIND_SOURCE = "torch_bind.cpp"
+BIND = os.path.join(HERE, "_torch_bind.so")
 
 
 def hipcc() -> str:
@@ -42,6 +47,20 @@ def _hip_flags():
     return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-Wall", "-Wno-unused-function", f"-I{os.path.join(ROOT, 'include')}"]
+
+
+def _torch_dir() -> str:
+    import torch
+    return os.path.dirname(torch.__file__)
+
+
+def _bind_compile(obj: str, torch_dir: str):
+    import torch
+    inc = [os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}"]
+            + [x for d in inc for x in ("-isystem", d)] + ["-c", os.path.join(CSRC, BIND_SOURCE), "-o", obj])
 
 
 def _run(cmd):
@@ -67,13 +86,21 @@ def build(verbose: bool = False) -> str:
         jobs.append(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-I{os.path.join(ROOT, 'include')}",
                      "-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
+    torch_dir = _torch_dir()
+    bind_obj = os.path.join(BUILD, BIND_SOURCE.replace(".", "_") + ".o")
+    jobs.append(_bind_compile(bind_obj, torch_dir))
     with cf.ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
         for res in ex.map(_run, jobs):
             if verbose and (res.stdout or res.stderr):
                 print(res.stdout + res.stderr)
     tmp = LIB + ".tmp"
-    _run([cc, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + objs)
+    _run([cc, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-Wl,-soname,libspecfp8.so", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    # torch's own libraries are loaded by `import torch` before the binding is
+    tmp = BIND + ".tmp"
+    _run(["g++", "-shared", "-o", tmp, bind_obj, f"-L{HERE}", "-lspecfp8", "-Wl,-rpath,$ORIGIN",
+          f"-L{os.path.join(torch_dir, 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
+    os.replace(tmp, BIND)
     return LIB
 
 
