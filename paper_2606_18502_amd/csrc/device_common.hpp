@@ -13,16 +13,8 @@ __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) {
     return __uint_as_float(bits16 << 16);
 }
 
-// fp32 -> bf16 bit pattern, round to nearest even (finite inputs; NaN stays NaN).
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0u;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-
 // Two fp32 values -> two bf16 bit patterns (a in the low half) with the
-// hardware conversion: round to nearest even, as f32_to_bf16_rne.
+// hardware conversion: round to nearest even (NaN stays NaN).
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t f32_to_bf16x2(float a, float b) {
@@ -36,11 +28,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16x2(float a, float b) {
 // in fp32 on the hardware exp2 and reciprocal (about 1 ulp each): the bf16
 // rounding of h only differs from an exact evaluation at near-ties.  Large
 // |g| saturate correctly: 2^(+big) = inf gives rcp = 0 (silu -> -0), and
-// 2^(-big) = 0 gives silu = g.
-__device__ __forceinline__ float silu_mul_bf16(float g, float u) {
+// 2^(-big) = 0 gives silu = g.  Two values, packed (the first in the low half).
+__device__ __forceinline__ float silu_mul(float g, float u) {
     const float e = __builtin_amdgcn_exp2f(g * -1.44269504088896341f);
     const float sg = g * __builtin_amdgcn_rcpf(1.0f + e);
-    return bf16_to_f32(f32_to_bf16_rne(sg * u));
+    return sg * u;
+}
+__device__ __forceinline__ uint32_t silu_mul_bf16x2(float g0, float u0, float g1, float u1) {
+    return f32_to_bf16x2(silu_mul(g0, u0), silu_mul(g1, u1));
 }
 
 // Unpack 8 bf16 values held in a 16-byte vector.
@@ -112,29 +107,16 @@ __device__ __forceinline__ double wave_sum_d(double v) {
     return v;
 }
 
-// Block-wide max / sum for blocks of up to 1024 threads; `red` holds >= 16 floats.
-// The reduction order is fixed, so results are deterministic.
+// Block-wide max for blocks of up to 1024 threads; `red` holds >= 16 floats and
+// is not in use by the block when this is called.
 __device__ __forceinline__ float block_max(float v, float* red) {
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int nw = (blockDim.x + kWave - 1) / kWave;
     v = wave_max(v);
-    __syncthreads();
     if (lane == 0) red[w] = v;
     __syncthreads();
     float r = red[0];
     for (int i = 1; i < nw; ++i) r = fmaxf(r, red[i]);
-    return r;
-}
-
-__device__ __forceinline__ float block_sum(float v, float* red) {
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int nw = (blockDim.x + kWave - 1) / kWave;
-    v = wave_sum(v);
-    __syncthreads();
-    if (lane == 0) red[w] = v;
-    __syncthreads();
-    float r = red[0];
-    for (int i = 1; i < nw; ++i) r += red[i];
     return r;
 }
 

@@ -489,13 +489,13 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, const v4f (&acc)
                 // column), lanes with kg >= 2 the matching up values
                 const float y[4] = {__uint_as_float(o.x << 16), __uint_as_float(o.x & 0xffff0000u),
                                     __uint_as_float(o.y << 16), __uint_as_float(o.y & 0xffff0000u)};
-                float h[4];
+                float up[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) h[r] = silu_mul_bf16(y[r], __shfl_xor(y[r], 32, 64));
+                for (int r = 0; r < 4; ++r) up[r] = __shfl_xor(y[r], 32, 64);
                 const int hc = (n0 + (wn * WTN + i) * 16) / 2 + 4 * kg;    // first h column of this lane
                 if (kg < 2 && (!EDGE || (m < g.M && hc < g.silu_inter))) {
-                    o.x = (__float_as_uint(h[0]) >> 16) | (__float_as_uint(h[1]) & 0xffff0000u);
-                    o.y = (__float_as_uint(h[2]) >> 16) | (__float_as_uint(h[3]) & 0xffff0000u);
+                    o.x = silu_mul_bf16x2(y[0], up[0], y[1], up[1]);
+                    o.y = silu_mul_bf16x2(y[2], up[2], y[3], up[3]);
                     *reinterpret_cast<uint2*>(row + hc) = o;
                 }
             } else if (!EDGE || n + 3 < g.N) {

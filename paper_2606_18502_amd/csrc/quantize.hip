@@ -3,9 +3,11 @@
 //
 // One workgroup owns one row.  The row is read from HBM once with 16-byte
 // loads (8 bf16 per load, consecutive threads on consecutive 16-byte chunks,
-// so every wave reads 1 KiB contiguous per instruction) and kept in
-// registers; the block reduces max|v| (wave shuffles, then LDS across waves),
-// derives the scale, and encodes the registers it already holds.  HBM traffic
+// so every wave reads 1 KiB contiguous per instruction), all issued before any
+// is used, and kept in registers as packed bf16; the block reduces max|v| (wave
+// shuffles, then LDS across waves), derives the scale, and encodes the
+// registers it already holds ([4096, 14336]: 29.6 us, 5.9 TB/s; 31.4 with the
+// loads issued one by one into fp32 registers).  HBM traffic
 // is therefore the algorithmic 2 bytes in + 1 byte out per element (4 + 1 for
 // the SiLU-gated input) plus 4 bytes of scale per row.  Rows wider than
 // 65536 elements take a second pass that re-reads the row.
@@ -19,29 +21,60 @@ namespace {
 constexpr int kQThreads = 256;       // threads of the element-wise kernel
 constexpr int kQMaxThreads = 1024;   // threads per row of the row kernel, at most
 
+// One chunk of 8 input values as they are loaded: the bf16 values themselves,
+// or the gate and up values of the SiLU-gated input.
 template <int IN_KIND>
-__device__ __forceinline__ void load_chunk(const uint16_t* __restrict__ xrow, int64_t cols,
-                                           int64_t c, float v[8]) {
-    if (IN_KIND == 0) {
-        const uint4 a = *reinterpret_cast<const uint4*>(xrow + c * 8);
-        unpack8(a, v);
+struct RawChunk {
+    uint4 a;
+    uint4 b[IN_KIND];     // (IN_KIND 1: the up values)
+};
+
+template <int IN_KIND>
+__device__ __forceinline__ RawChunk<IN_KIND> load_raw(const uint16_t* __restrict__ xrow, int64_t cols, int64_t c) {
+    RawChunk<IN_KIND> r;
+    r.a = *reinterpret_cast<const uint4*>(xrow + c * 8);
+    if constexpr (IN_KIND == 1) r.b[0] = *reinterpret_cast<const uint4*>(xrow + cols + c * 8);
+    return r;
+}
+
+// The 8 values to encode, packed bf16 (h of the gated input is a bf16 value by
+// definition, so nothing is lost by keeping it packed until it is encoded).
+template <int IN_KIND>
+__device__ __forceinline__ uint4 chunk_values(const RawChunk<IN_KIND>& r) {
+    if constexpr (IN_KIND == 0) {
+        return r.a;
     } else {
-        const uint4 a = *reinterpret_cast<const uint4*>(xrow + c * 8);
-        const uint4 b = *reinterpret_cast<const uint4*>(xrow + cols + c * 8);
         float g[8], u[8];
-        unpack8(a, g);
-        unpack8(b, u);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = silu_mul_bf16(g[e], u[e]);
+        unpack8(r.a, g);
+        unpack8(r.b[0], u);
+        uint4 h;
+        h.x = silu_mul_bf16x2(g[0], u[0], g[1], u[1]);
+        h.y = silu_mul_bf16x2(g[2], u[2], g[3], u[3]);
+        h.z = silu_mul_bf16x2(g[4], u[4], g[5], u[5]);
+        h.w = silu_mul_bf16x2(g[6], u[6], g[7], u[7]);
+        return h;
     }
 }
 
-__device__ __forceinline__ void store_codes(uint8_t* __restrict__ qrow, int64_t c, const float v[8],
-                                            float inv) {
+__device__ __forceinline__ float abs_max8(const uint4& h, float amax) {
+    float v[8];
+    unpack8(h, v);
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) amax = fmaxf(fmaxf(amax, fabsf(v[e])), fabsf(v[e + 1]));
+    return amax;
+}
+
+__device__ __forceinline__ void store_codes(uint8_t* __restrict__ qrow, int64_t c, const float (&v)[8], float inv) {
     uint2 o;
     o.x = e4m3x4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
     o.y = e4m3x4(v[4] * inv, v[5] * inv, v[6] * inv, v[7] * inv);
     *reinterpret_cast<uint2*>(qrow + c * 8) = o;
+}
+
+__device__ __forceinline__ void store_codes(uint8_t* __restrict__ qrow, int64_t c, const uint4& h, float inv) {
+    float v[8];
+    unpack8(h, v);
+    store_codes(qrow, c, v, inv);
 }
 
 __device__ __forceinline__ void row_scale(float amax, float* s_out, float* inv_out) {
@@ -58,8 +91,11 @@ __device__ __forceinline__ void calibrate_max(float* running, float s) {
     atomicMax(reinterpret_cast<unsigned int*>(running), __float_as_uint(s));
 }
 
-// MODE 0: per-row scales (written); 1: one given scale; 2: calibration only.
-// NCH > 0: the row lives in registers (NCH chunks of 8 per thread).
+// Per-row scales (MODE 0, written) or calibration only (MODE 2): one workgroup
+// per row.
+// NCH > 0: the row lives in registers, NCH chunks of 8 per thread, all of them
+// loaded before any is used (one memory round trip; a chunk past the row's end
+// reloads its last one and is not stored).
 // NCH == 0: rows too wide for registers; amax pass and encode pass each read the row.
 template <int IN_KIND, int MODE, int NCH>
 __global__ __launch_bounds__(kQMaxThreads) void quantize_rows_kernel(
@@ -73,65 +109,84 @@ __global__ __launch_bounds__(kQMaxThreads) void quantize_rows_kernel(
     const int t = threadIdx.x;
     const int nt = blockDim.x;
 
+    uint4 h[NCH > 0 ? NCH : 1];
+    float amax = 0.0f;
     if constexpr (NCH > 0) {
-        float v[NCH][8];
-        float amax = 0.0f;
+        RawChunk<IN_KIND> raw[NCH];
+#pragma unroll
+        for (int j = 0; j < NCH; ++j)
+            raw[j] = load_raw<IN_KIND>(xrow, cols, min(t + (int64_t)j * nt, nchunks - 1));
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
-            const int64_t c = t + (int64_t)j * nt;
-            if (c < nchunks) {
-                load_chunk<IN_KIND>(xrow, cols, c, v[j]);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(v[j][e]));
-            }
-        }
-        float s, inv;
-        if (MODE == 2) {
-            amax = block_max(amax, red);
-            row_scale(amax, &s, &inv);
-            if (t == 0) calibrate_max(scales, s);
-            return;
-        }
-        if (MODE == 0) {
-            amax = block_max(amax, red);
-            row_scale(amax, &s, &inv);
-            if (t == 0) scales[row] = s;
-        } else {
-            s = scales[0];
-            inv = (float)(1.0 / (double)s);
-        }
-#pragma unroll
-        for (int j = 0; j < NCH; ++j) {
-            const int64_t c = t + (int64_t)j * nt;
-            if (c < nchunks) store_codes(qrow, c, v[j], inv);
+            h[j] = chunk_values<IN_KIND>(raw[j]);
+            amax = abs_max8(h[j], amax);
         }
     } else {
-        float s, inv;
-        if (MODE != 1) {
-            float amax = 0.0f;
-            for (int64_t c = t; c < nchunks; c += nt) {
-                float v[8];
-                load_chunk<IN_KIND>(xrow, cols, c, v);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(v[e]));
-            }
-            amax = block_max(amax, red);
-            row_scale(amax, &s, &inv);
-            if (MODE == 2) {
-                if (t == 0) calibrate_max(scales, s);
-                return;
-            }
-            if (t == 0) scales[row] = s;
-        } else {
-            s = scales[0];
-            inv = (float)(1.0 / (double)s);
-        }
-        for (int64_t c = t; c < nchunks; c += nt) {
-            float v[8];
-            load_chunk<IN_KIND>(xrow, cols, c, v);
-            store_codes(qrow, c, v, inv);
-        }
+        for (int64_t c = t; c < nchunks; c += nt)
+            amax = abs_max8(chunk_values<IN_KIND>(load_raw<IN_KIND>(xrow, cols, c)), amax);
     }
+    float s, inv;
+    row_scale(block_max(amax, red), &s, &inv);
+    if constexpr (MODE == 2) {
+        if (t == 0) calibrate_max(scales, s);
+        return;
+    }
+    if (t == 0) scales[row] = s;
+    if constexpr (NCH > 0) {
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) {
+            const int64_t c = t + (int64_t)j * nt;
+            if (c < nchunks) store_codes(qrow, c, h[j], inv);
+        }
+    } else {
+        for (int64_t c = t; c < nchunks; c += nt)
+            store_codes(qrow, c, chunk_values<IN_KIND>(load_raw<IN_KIND>(xrow, cols, c)), inv);
+    }
+}
+
+// One given scale, one workgroup per row: a thread encodes its chunks one after
+// the other, or (PAIR) loads and unpacks its two chunks first.
+template <int IN_KIND, bool PAIR>
+__global__ __launch_bounds__(kQMaxThreads) void quantize_static_rows_kernel(
+    const uint16_t* __restrict__ x, int64_t cols, int64_t ld_x, const float* __restrict__ scale,
+    uint8_t* __restrict__ q, int64_t ld_q) {
+    const int64_t row = blockIdx.x;
+    const int64_t nchunks = cols / 8;
+    const uint16_t* xrow = x + row * ld_x;
+    uint8_t* qrow = q + row * ld_q;
+    const int t = threadIdx.x, nt = blockDim.x;
+    if constexpr (PAIR) {
+        float v[2][8];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (t + j * nt < nchunks) unpack8(chunk_values<IN_KIND>(load_raw<IN_KIND>(xrow, cols, t + j * nt)), v[j]);
+        const float inv = (float)(1.0 / (double)scale[0]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (t + j * nt < nchunks) store_codes(qrow, t + j * nt, v[j], inv);
+    } else {
+        const float inv = (float)(1.0 / (double)scale[0]);
+        auto encode = [&](int64_t c) {
+            store_codes(qrow, c, chunk_values<IN_KIND>(load_raw<IN_KIND>(xrow, cols, c)), inv);
+        };
+        if (t < nchunks) encode(t);
+        if (t + nt < nchunks) encode(t + nt);
+        for (int64_t c = t + 2 * nt; c < nchunks; c += nt) encode(c);
+    }
+}
+
+// One given scale and few rows: with no row maximum to reduce, the columns of
+// a row are shared by per_row workgroups, one chunk per thread.
+template <int IN_KIND>
+__global__ __launch_bounds__(kQThreads) void quantize_static_kernel(
+    const uint16_t* __restrict__ x, int64_t cols, int64_t ld_x, const float* __restrict__ scale,
+    uint8_t* __restrict__ q, int64_t ld_q, unsigned per_row) {
+    const int64_t row = blockIdx.x / per_row;
+    const int64_t c = (int64_t)(blockIdx.x % per_row) * kQThreads + threadIdx.x;
+    if (c >= cols / 8) return;
+    const RawChunk<IN_KIND> raw = load_raw<IN_KIND>(x + row * ld_x, cols, c);
+    const float inv = (float)(1.0 / (double)scale[0]);
+    store_codes(q + row * ld_q, c, chunk_values<IN_KIND>(raw), inv);
 }
 
 __global__ __launch_bounds__(kQThreads) void silu_mul_bf16_kernel(
@@ -140,14 +195,8 @@ __global__ __launch_bounds__(kQThreads) void silu_mul_bf16_kernel(
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= cols / 8) return;
     for (int64_t row = blockIdx.y; row < rows; row += gridDim.y) {
-        float v[8];
-        load_chunk<1>(x + row * ld_x, cols, c, v);
-        uint4 o;
-        o.x = f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16);
-        o.y = f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16);
-        o.z = f32_to_bf16_rne(v[4]) | (f32_to_bf16_rne(v[5]) << 16);
-        o.w = f32_to_bf16_rne(v[6]) | (f32_to_bf16_rne(v[7]) << 16);
-        *reinterpret_cast<uint4*>(h + row * ld_h + c * 8) = o;
+        *reinterpret_cast<uint4*>(h + row * ld_h + c * 8) =
+            chunk_values<1>(load_raw<1>(x + row * ld_x, cols, c));
     }
 }
 
@@ -186,19 +235,16 @@ __global__ __launch_bounds__(kQThreads) void clip_count_kernel(const uint16_t* _
 }
 
 template <int IN_KIND, int MODE>
-hipError_t launch_quantize_t(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld_x,
-                             float* scales, uint8_t* q, int64_t ld_q, hipStream_t stream) {
-    // One workgroup per row, wide enough that a thread holds at most 4
-    // chunks of 8 (up to 1024 threads; wider rows hold up to 8 per thread or
-    // take the two-pass path).  With a given scale (no row maximum, so no
-    // workgroup barrier) at most 2 chunks per thread: more waves per row keep
-    // more loads in flight (measured on [4096, 14336] rows: 31.5 -> 29.9 us);
-    // where the row maximum is reduced across the workgroup, the extra waves
-    // cost more at the barrier than they gain (32.8 -> 34.1 us).
+hipError_t launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld_x, float* scales, uint8_t* q,
+                       int64_t ld_q, hipStream_t stream) {
+    // One workgroup per row, wide enough that a thread holds at most 8 chunks
+    // (up to 1024 threads; wider rows take the two-pass path): few waves with
+    // many loads in flight each reach the reduction's barrier soonest (8 chunks
+    // against 4, 2 or 1: [1005, 14336] rows 9.7 us against 10.1, 11.1 and 10.1,
+    // the SiLU-gated [320, 14336] 8.0 against 8.3, 8.6 and 8.7).
     const int64_t nchunks = cols / 8;
-    const int64_t per_thread_max = MODE == 1 ? 2 : 4;
     int threads = 256;
-    while (threads < kQMaxThreads && nchunks > per_thread_max * (int64_t)threads) threads *= 2;
+    while (threads < kQMaxThreads && nchunks > 8 * (int64_t)threads) threads *= 2;
     if (nchunks < threads) threads = (int)(((nchunks + 63) / 64) * 64);
     const int64_t per = (nchunks + threads - 1) / threads;
     dim3 grid((unsigned)rows), block(threads);
@@ -224,21 +270,47 @@ hipError_t launch_quantize_t(const uint16_t* x, int64_t rows, int64_t cols, int6
     return hipGetLastError();
 }
 
+template <int IN_KIND>
+hipError_t launch_static(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld_x, const float* scale, uint8_t* q,
+                         int64_t ld_q, hipStream_t stream) {
+    // Rows wider than one chunk per thread are split over workgroups until the
+    // chip is full several times over (SiLU-gated 14336 columns: 64 rows 4.0 ->
+    // 2.8 us, 320 rows 7.7 -> 6.5; 1005 rows 13.9 -> 14.3, so not beyond;
+    // [4000, 904] rows 3.8 -> 4.3).  Larger ones take one workgroup per row,
+    // which encodes chunk by chunk ([4096, 4096] 10.2 us; 10.6 when a thread's
+    // chunks are loaded first) but for the longest streams of plain rows
+    // ([4096, 14336] 28.9 -> 28.4 us the other way round).
+    const int64_t nchunks = cols / 8;
+    if (nchunks <= kQThreads || rows * nchunks > 600000) {
+        int threads = 64;
+        while (threads < kQMaxThreads && nchunks > (threads < kQThreads ? 1 : 2) * (int64_t)threads) threads *= 2;
+        const dim3 grid((unsigned)rows), block(threads);
+        if (IN_KIND == 0 && rows * nchunks > 5000000 && nchunks <= 2 * (int64_t)threads)
+            hipLaunchKernelGGL((quantize_static_rows_kernel<IN_KIND, true>), grid, block, 0, stream, x, cols, ld_x, scale,
+                               q, ld_q);
+        else
+            hipLaunchKernelGGL((quantize_static_rows_kernel<IN_KIND, false>), grid, block, 0, stream, x, cols, ld_x,
+                               scale, q, ld_q);
+        return hipGetLastError();
+    }
+    const unsigned per_row = (unsigned)((nchunks + kQThreads - 1) / kQThreads);
+    hipLaunchKernelGGL(quantize_static_kernel<IN_KIND>, dim3((unsigned)rows * per_row), dim3(kQThreads), 0, stream, x,
+                       cols, ld_x, scale, q, ld_q, per_row);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_quantize(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld_x, int in_kind,
                            int mode, float* scales, uint8_t* q, int64_t ld_q, hipStream_t stream) {
-    if (in_kind == 0 && mode == 0)
-        return launch_quantize_t<0, 0>(x, rows, cols, ld_x, scales, q, ld_q, stream);
-    if (in_kind == 0 && mode == 1)
-        return launch_quantize_t<0, 1>(x, rows, cols, ld_x, scales, q, ld_q, stream);
-    if (in_kind == 0 && mode == 2)
-        return launch_quantize_t<0, 2>(x, rows, cols, ld_x, scales, q, ld_q, stream);
-    if (in_kind == 1 && mode == 0)
-        return launch_quantize_t<1, 0>(x, rows, cols, ld_x, scales, q, ld_q, stream);
-    if (in_kind == 1 && mode == 2)
-        return launch_quantize_t<1, 2>(x, rows, cols, ld_x, scales, q, ld_q, stream);
-    return launch_quantize_t<1, 1>(x, rows, cols, ld_x, scales, q, ld_q, stream);
+    if (mode == 1)
+        return in_kind == 0 ? launch_static<0>(x, rows, cols, ld_x, scales, q, ld_q, stream)
+                            : launch_static<1>(x, rows, cols, ld_x, scales, q, ld_q, stream);
+    if (in_kind == 0)
+        return mode == 0 ? launch_rows<0, 0>(x, rows, cols, ld_x, scales, q, ld_q, stream)
+                         : launch_rows<0, 2>(x, rows, cols, ld_x, scales, q, ld_q, stream);
+    return mode == 0 ? launch_rows<1, 0>(x, rows, cols, ld_x, scales, q, ld_q, stream)
+                     : launch_rows<1, 2>(x, rows, cols, ld_x, scales, q, ld_q, stream);
 }
 
 hipError_t launch_clip_count(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld_x, const float* scale,

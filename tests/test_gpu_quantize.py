@@ -200,3 +200,29 @@ def test_silu_mul_quantize_verify_step_width():
     say(f"h differs on {int((diff != 0).sum())} of {diff.size}; code steps {int((step != 0).sum())}")
     assert np.max(step, initial=0) <= 1
     assert np.mean(step != 0) <= 1e-4
+
+
+@pytest.mark.parametrize("rows,cols,silu", [
+    (3, 2056, False), (5, 14336, True), (33, 16384, False),     # one given scale, few rows: a row over several workgroups
+    (2600, 16384, False),                                       # the longest streams, two chunks per thread
+    (4700, 1032, True), (2, 40000, False), (1, 65544, True),    # one workgroup per row; beyond two chunks; two passes
+])
+def test_row_splits_per_tensor_and_per_row(rows, cols, silu):
+    """Both scale modes at the edges of the launch rules; every code of up to
+    64 rows against the oracle."""
+    p = need_gpu()
+    say(f"quantize splits rows={rows} cols={cols} silu={silu}")
+    w = 2 * cols if silu else cols
+    xb = wl.linear_activations(rows, w, seed=rows + cols)
+    x = dev_bf16(xb)
+    v = xb
+    if silu:
+        v = host_bf16_bits(p.silu_mul(x))            # the device's own h: the codes are bit-exact given it
+    pick = np.unique(np.linspace(0, rows - 1, min(rows, 64)).astype(int))
+    q, s = p.quantize(x, silu_mul=silu)
+    q_ref, s_ref = oq.quantize_rows(v[pick])
+    np.testing.assert_array_equal(host(s)[pick], s_ref)
+    np.testing.assert_array_equal(host(q)[pick], q_ref)
+    st = np.float32(0.0123)
+    q, _ = p.quantize(x, per_tensor_scale=dev_f32([st]), silu_mul=silu)
+    np.testing.assert_array_equal(host(q)[pick], oq.quantize_per_tensor(v[pick], st))
