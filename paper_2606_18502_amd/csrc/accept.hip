@@ -34,6 +34,7 @@
 // results are deterministic.
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -110,44 +111,91 @@ __device__ __forceinline__ int64_t slice_vec(int64_t e0, int j, int lane) {
     return e0 + ((int64_t)j * kWave + lane) * 8;
 }
 
-// Issue the loads of one slice (vector path only).  Out-of-range vectors load
-// the last full vector of the slice instead (always in bounds, V % 8 == 0);
-// their values are masked where they are used.  The loads are nontemporal:
+// How the logit rows are read, 8 logits at a time:
+//   kAligned  rows on 16-byte boundaries, V % 8 == 0: no group is cut
+//   kLoose    any other rows of at least 8 logits: the same 16-byte loads, from
+//             any 2-byte boundary (global memory takes them so); a group that
+//             runs past the row's end is read from the row's last 8 logits
+//   kShort    rows of fewer than 8 logits, element by element
+// What bounds 2-byte loads is their count: greedy over [104, 32001] took 17.5 us
+// with them and 8.3 us with kLoose.
+enum RowLoad { kAligned, kLoose, kShort };
+typedef unsigned int stream_u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int loose_u32x4 __attribute__((ext_vector_type(4), aligned(2)));
+
+inline RowLoad row_load(int64_t V, const void* zt, const void* zd) {
+    if (V < 8) return kShort;
+    return V % 8 == 0 && (uintptr_t)zt % 16 == 0 && (uintptr_t)zd % 16 == 0 ? kAligned : kLoose;
+}
+
+// The 8 logits at e of a row.  Where the group runs past e1 (or lies past it)
+// the last 8 before e1 are read instead (cut8 puts a cut group right).
+template <RowLoad LD, bool STREAM>
+__device__ __forceinline__ uint4 load8(const uint16_t* __restrict__ row, int64_t e, int64_t e1) {
+    if constexpr (LD == kShort) {
+        uint32_t w[4];
+#pragma unroll
+        for (int q = 0; q < 8; q += 2)
+            w[q / 2] = (uint32_t)row[min((int64_t)q, e1 - 1)] | ((uint32_t)row[min((int64_t)q + 1, e1 - 1)] << 16);
+        return make_uint4(w[0], w[1], w[2], w[3]);
+    } else {
+        using Vec = std::conditional_t<LD == kAligned, stream_u32x4, loose_u32x4>;
+        const Vec* p = reinterpret_cast<const Vec*>(row + min(e, e1 - 8));
+        const Vec v = STREAM ? __builtin_nontemporal_load(p) : *p;
+        return make_uint4(v.x, v.y, v.z, v.w);
+    }
+}
+
+// Issue the loads of one slice.  Lanes past the slice's end load its last
+// group; their values are masked where they are used.  The loads are nontemporal:
 // the statistics pass reads each logit once, and cache-allocating loads of
 // 148 MB would push the model's weights and the dirty outputs of the layer
 // out of the Infinity Cache (measured in the verify step: the statistics pass
 // 31.1 -> 27.0 us, the next gate|up and down GEMMs ~1 us faster each; the
 // sampling kernel's re-read of the residual rows then comes from HBM).
-typedef unsigned int stream_u32x4 __attribute__((ext_vector_type(4)));
-template <bool VEC>
+template <RowLoad LD>
 __device__ __forceinline__ void load_slice(const uint16_t* __restrict__ row, int64_t e0, int64_t e1, int lane,
                                            Raw& raw) {
-    if (!VEC) return;
 #pragma unroll
-    for (int j = 0; j < kVecs; ++j) {
-        const int64_t e = min(slice_vec(e0, j, lane), e1 - 8);
-        const stream_u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const stream_u32x4*>(row + e));
-        raw[j] = make_uint4(v.x, v.y, v.z, v.w);
-    }
+    for (int j = 0; j < kVecs; ++j) raw[j] = load8<LD, true>(row, slice_vec(e0, j, lane), e1);
 }
 
-// Element e + q of a group of 8 starting at e < e1 exists.  With vector
-// loads, V and every range end are multiples of 8, so the whole group does.
-template <bool VEC>
-__device__ __forceinline__ bool in8(int64_t e, int q, int64_t e1) { return VEC || e + q < e1; }
-
-// 8 values starting at e (< e1): from the loaded vector, or element-wise when
-// V is not a multiple of 8 (no vector loads then).  Elements >= e1 read `fill`.
-template <bool VEC>
-__device__ __forceinline__ void vals8(const uint16_t* __restrict__ row, const uint4& raw, int64_t e, int64_t e1,
-                                      float fill, float out[8]) {
-    if (VEC) {
-        unpack8(raw, out);
-    } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) out[q] = (e + q < e1) ? bf16_to_f32(row[e + q]) : fill;
+// Puts the group at e right where it is cut by e1: load8 read the last 8
+// logits before e1, which are shifted down to start at e; the elements from
+// e1 on become the bf16 `fill`.
+template <RowLoad LD>
+__device__ __forceinline__ void cut8(uint4& raw, int64_t e, int64_t e1, uint16_t fill) {
+    if (LD == kAligned || e + 8 <= e1 || e >= e1) return;
+    uint64_t lo = raw.x | ((uint64_t)raw.y << 32), hi = raw.z | ((uint64_t)raw.w << 32);
+    const int sh = LD == kShort ? 0 : 16 * (int)(8 - (e1 - e));
+    if (sh >= 64) {
+        lo = hi >> (sh - 64);
+    } else if (sh > 0) {
+        lo = (lo >> sh) | (hi << (64 - sh));
+        hi >>= sh;
     }
+    const int keep = 16 * (int)(e1 - e);                     // 16 .. 112 bits
+    const uint64_t f = 0x0001000100010001ull * fill;
+    const uint64_t ml = keep >= 64 ? ~0ull : (1ull << keep) - 1;
+    const uint64_t mh = keep > 64 ? (1ull << (keep - 64)) - 1 : 0;
+    lo = (lo & ml) | (f & ~ml);
+    hi = (hi & mh) | (f & ~mh);
+    raw = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
+
+// cut8 over one slice's groups.
+template <RowLoad LD>
+__device__ __forceinline__ void cut_slice(Raw& raw, int64_t e0, int64_t e1, int lane, uint16_t fill) {
+    if (LD == kAligned || e1 - e0 == kSlice) return;
+#pragma unroll
+    for (int j = 0; j < kVecs; ++j) cut8<LD>(raw[j], slice_vec(e0, j, lane), e1, fill);
+}
+constexpr uint16_t kBf16NaN = 0x7fc0, kBf16NegInf = 0xff80;
+
+// Element e + q of a group of 8 starting at e < e1 exists (with kAligned every
+// range end is a multiple of 8, so the whole group does).
+template <RowLoad LD>
+__device__ __forceinline__ bool in8(int64_t e, int q, int64_t e1) { return LD == kAligned || e + q < e1; }
 
 // Workgroups of the streaming kernels: at most kStreamWavesPerCU waves per
 // compute unit, the items spread so that every wave takes the same count (but
@@ -172,7 +220,7 @@ inline unsigned stream_blocks(int64_t items, int cus) {
 // (C4 stochastic acceptance 46.4 -> 46.1 us).
 // Only the first a.sw waves of the grid stream (workgroups past them do side
 // work).
-template <bool VEC, class RowOf, class Body>
+template <RowLoad LD, class RowOf, class Body>
 __device__ __forceinline__ void stream_items(const AcceptArgs& a, RowOf row_of, Body body) {
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t gw = blockIdx.x * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -182,12 +230,12 @@ __device__ __forceinline__ void stream_items(const AcceptArgs& a, RowOf row_of, 
     auto clampi = [&](uint32_t it) { return it < a.items ? it : a.items - 1; };
     if (gw >= GW || gw >= a.items) return;
     Raw r0, r1;
-    load_slice<VEC>(row_of(gw / a.nslice), lo(gw), hi(gw), lane, r0);
+    load_slice<LD>(row_of(gw / a.nslice), lo(gw), hi(gw), lane, r0);
     for (uint32_t it = gw; it < a.items; it += 2 * GW) {
         const uint32_t n1 = clampi(it + GW), n2 = clampi(it + 2 * GW);
-        load_slice<VEC>(row_of(n1 / a.nslice), lo(n1), hi(n1), lane, r1);
+        load_slice<LD>(row_of(n1 / a.nslice), lo(n1), hi(n1), lane, r1);
         body(it, r0);
-        load_slice<VEC>(row_of(n2 / a.nslice), lo(n2), hi(n2), lane, r0);
+        load_slice<LD>(row_of(n2 / a.nslice), lo(n2), hi(n2), lane, r0);
         if (it + GW < a.items) body(it + GW, r1);
     }
 }
@@ -199,16 +247,16 @@ __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
 }
 
 // Lane maximum of the logits of one slice (8-element groups, v_max3 pairs).
-// Missing elements (non-vector path past e1) read NaN, which fmaxf ignores.
-template <bool VEC, bool FULL>
-__device__ __forceinline__ float slice_max(const uint16_t* z, const Raw& raw, int64_t e0, int64_t e1, int lane) {
+// Elements past e1 in a cut group hold NaN, which fmaxf ignores, or -inf.
+template <bool FULL>
+__device__ __forceinline__ float slice_max(const Raw& raw, int64_t e0, int64_t e1, int lane) {
     float zm = -INFINITY;
 #pragma unroll
     for (int j = 0; j < kVecs; ++j) {
         const int64_t e = slice_vec(e0, j, lane);
         if (FULL || e < e1) {
             float v[8];
-            vals8<VEC>(z, raw[j], e, e1, __builtin_nanf(""), v);
+            unpack8(raw[j], v);
 #pragma unroll
             for (int q = 0; q < 8; q += 2) zm = fmaxf(fmaxf(zm, v[q]), v[q + 1]);
         }
@@ -217,9 +265,9 @@ __device__ __forceinline__ float slice_max(const uint16_t* z, const Raw& raw, in
 }
 
 // (max logit, lowest index holding it) of one slice, reduced over the wave.
-template <bool VEC, bool FULL>
-__device__ __forceinline__ float2 slice_argmax(const uint16_t* z, const Raw& raw, int64_t e0, int64_t e1, int lane) {
-    const float M = wave_max(slice_max<VEC, FULL>(z, raw, e0, e1, lane));
+template <bool FULL>
+__device__ __forceinline__ float2 slice_argmax(const Raw& raw, int64_t e0, int64_t e1, int lane) {
+    const float M = wave_max(slice_max<FULL>(raw, e0, e1, lane));
     // lowest index of M in the lane: scan backwards, the last hit wins
     int bi = 0x7fffffff;
 #pragma unroll
@@ -227,7 +275,7 @@ __device__ __forceinline__ float2 slice_argmax(const uint16_t* z, const Raw& raw
         const int64_t e = slice_vec(e0, j, lane);
         if (FULL || e < e1) {
             float v[8];
-            vals8<VEC>(z, raw[j], e, e1, __builtin_nanf(""), v);
+            unpack8(raw[j], v);
 #pragma unroll
             for (int q = 7; q >= 0; --q) bi = (v[q] == M) ? (int)(e + q) : bi;
         }
@@ -235,16 +283,16 @@ __device__ __forceinline__ float2 slice_argmax(const uint16_t* z, const Raw& raw
     return make_float2(M, __int_as_float(wave_min_i32(bi)));
 }
 
-template <bool VEC>
+template <RowLoad LD>
 __global__ __launch_bounds__(kAThreads) void greedy_partial_kernel(AcceptArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     auto row_of = [&](uint32_t row) { return a.zt + (int64_t)row * a.V; };
-    stream_items<VEC>(a, row_of, [&](uint32_t it, const Raw& raw) {
+    stream_items<LD>(a, row_of, [&](uint32_t it, Raw& raw) {
         const uint32_t row = it / a.nslice, c = it % a.nslice;
-        const uint16_t* z = row_of(row);
         const int64_t e0 = (int64_t)c * kSlice, e1 = min(e0 + kSlice, a.V);
-        const float2 r = (VEC && e1 - e0 == kSlice) ? slice_argmax<VEC, true>(z, raw, e0, e1, lane)
-                                                    : slice_argmax<VEC, false>(z, raw, e0, e1, lane);
+        cut_slice<LD>(raw, e0, e1, lane, kBf16NaN);
+        const float2 r = (e1 - e0 == kSlice) ? slice_argmax<true>(raw, e0, e1, lane)
+                                                    : slice_argmax<false>(raw, e0, e1, lane);
         if (lane == 0) a.stats[(int64_t)row * a.nslice + c] = r;
     });
 }
@@ -320,10 +368,10 @@ __global__ __launch_bounds__(1024) void greedy_final_kernel(AcceptArgs a) {
 // (m, sum 2^(t - m)) of t = z * c2 over one slice, reduced over the wave:
 // the wave maximum first (c2 > 0, so max t = fl(max z * c2)), then one
 // exponential per element with the wave's m, so no partial sum is rescaled.
-template <bool VEC, bool FULL>
-__device__ __forceinline__ float2 slice_stats(const uint16_t* z, const Raw& raw, int64_t e0, int64_t e1, int lane,
+template <bool FULL>
+__device__ __forceinline__ float2 slice_stats(const Raw& raw, int64_t e0, int64_t e1, int lane,
                                               float c2) {
-    const float M = wave_max(slice_max<VEC, FULL>(z, raw, e0, e1, lane)) * c2;
+    const float M = wave_max(slice_max<FULL>(raw, e0, e1, lane)) * c2;
     float s = 0.0f;
     if (M != -INFINITY) {
 #pragma unroll
@@ -331,7 +379,7 @@ __device__ __forceinline__ float2 slice_stats(const uint16_t* z, const Raw& raw,
             const int64_t e = slice_vec(e0, j, lane);
             if (FULL || e < e1) {
                 float v[8];
-                vals8<VEC>(z, raw[j], e, e1, -INFINITY, v);
+                unpack8(raw[j], v);
 #pragma unroll
                 for (int q = 0; q < 8; ++q) s += __builtin_amdgcn_exp2f(fmaf(v[q], c2, -M));
             }
@@ -375,7 +423,7 @@ __device__ __forceinline__ float2 merge_row_ms(const float2* st, uint32_t n, int
     return make_float2(M, Z);
 }
 
-template <bool VEC>
+template <RowLoad LD>
 __global__ __launch_bounds__(kAThreads) void stoch_stats_kernel(AcceptArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     if (a.tsm) {
@@ -418,13 +466,13 @@ __global__ __launch_bounds__(kAThreads) void stoch_stats_kernel(AcceptArgs a) {
         }
         return;
     }
-    stream_items<VEC>(a, row_of, [&](uint32_t it, const Raw& raw) {
+    stream_items<LD>(a, row_of, [&](uint32_t it, Raw& raw) {
         const uint32_t row = it / a.nslice, c = it % a.nslice;
-        const uint16_t* z = row_of(row);
         const int64_t e0 = (int64_t)c * kSlice, e1 = min(e0 + kSlice, a.V);
         if (c == 0 && (row % a.Rs) == 0 && lane == 0) a.ctr[row / a.Rs] = 0u;   // ticket of the sample kernel
-        const float2 r = (VEC && e1 - e0 == kSlice) ? slice_stats<VEC, true>(z, raw, e0, e1, lane, a.c2)
-                                                    : slice_stats<VEC, false>(z, raw, e0, e1, lane, a.c2);
+        cut_slice<LD>(raw, e0, e1, lane, kBf16NegInf);
+        const float2 r = (e1 - e0 == kSlice) ? slice_stats<true>(raw, e0, e1, lane, a.c2)
+                                                    : slice_stats<false>(raw, e0, e1, lane, a.c2);
         if (lane == 0) a.stats[(int64_t)row * a.nslice + c] = r;
     });
 }
@@ -448,25 +496,27 @@ __device__ __forceinline__ bool killed(const Dist& d, int64_t e) {
 // Probabilities of the 8 elements at e (< e1) from loaded vectors: with a
 // draft row (HAS_D) the residual max(0, p - q), else p with element `skip`
 // (the one-hot draft token, or -1) set to zero.
-template <bool VEC, bool HAS_D>
-__device__ __forceinline__ void dist8(const Dist& d, float c2, const uint4& rt, const uint4& rd, int64_t e,
+template <RowLoad LD, bool HAS_D>
+__device__ __forceinline__ void dist8(const Dist& d, float c2, uint4 rt, uint4 rd, int64_t e,
                                       int64_t e1, float r[8]) {
     float zt[8];
-    vals8<VEC>(d.zt_row, rt, e, e1, 0.0f, zt);
+    cut8<LD>(rt, e, e1, 0);
+    unpack8(rt, zt);
     if constexpr (HAS_D) {
         float zd[8];
-        vals8<VEC>(d.zd_row, rd, e, e1, 0.0f, zd);
+        cut8<LD>(rd, e, e1, 0);
+        unpack8(rd, zd);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const float p = __builtin_amdgcn_exp2f(fmaf(zt[q], c2, -d.mt)) * d.inv_zt;
             const float qq = __builtin_amdgcn_exp2f(fmaf(zd[q], c2, -d.md)) * d.inv_zd;
-            r[q] = in8<VEC>(e, q, e1) ? fmaxf(p - qq, 0.0f) : 0.0f;
+            r[q] = in8<LD>(e, q, e1) ? fmaxf(p - qq, 0.0f) : 0.0f;
         }
     } else {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const float p = __builtin_amdgcn_exp2f(fmaf(zt[q], c2, -d.mt)) * d.inv_zt;
-            r[q] = (in8<VEC>(e, q, e1) && e + q != d.skip && !killed(d, e + q)) ? p : 0.0f;
+            r[q] = (in8<LD>(e, q, e1) && e + q != d.skip && !killed(d, e + q)) ? p : 0.0f;
         }
     }
 }
@@ -485,16 +535,13 @@ __device__ __forceinline__ float dist1(const Dist& d, float c2, int64_t e) {
 
 // Mass of the range [e0, e1) of at most 64 elements (e0 < e1), in double.
 // The 8 vectors of the range are loaded before any is used.
-template <bool VEC, bool HAS_D>
+template <RowLoad LD, bool HAS_D>
 __device__ __forceinline__ double range_mass(const Dist& d, float c2, int64_t e0, int64_t e1) {
     Raw rt, rd;
-    if (VEC) {
 #pragma unroll
-        for (int j = 0; j < kVecs; ++j) {
-            const int64_t e = min(e0 + j * 8, e1 - 8);
-            rt[j] = *reinterpret_cast<const uint4*>(d.zt_row + e);
-            if (HAS_D) rd[j] = *reinterpret_cast<const uint4*>(d.zd_row + e);
-        }
+    for (int j = 0; j < kVecs; ++j) {
+        rt[j] = load8<LD, false>(d.zt_row, e0 + j * 8, e1);
+        if (HAS_D) rd[j] = load8<LD, false>(d.zd_row, e0 + j * 8, e1);
     }
     double m = 0.0;
 #pragma unroll
@@ -502,7 +549,7 @@ __device__ __forceinline__ double range_mass(const Dist& d, float c2, int64_t e0
         const int64_t e = e0 + j * 8;
         if (e < e1) {
             float r[8];
-            dist8<VEC, HAS_D>(d, c2, rt[j], rd[j], e, e1, r);
+            dist8<LD, HAS_D>(d, c2, rt[j], rd[j], e, e1, r);
             m += (((double)r[0] + (double)r[1]) + ((double)r[2] + (double)r[3])) +
                  (((double)r[4] + (double)r[5]) + ((double)r[6] + (double)r[7]));
         }
@@ -517,7 +564,7 @@ __device__ __forceinline__ double range_mass(const Dist& d, float c2, int64_t e0
 // that share a range add their sums by xor exchanges in a fixed order, and the
 // first of them stores the mass of range wv*64 + j*8 + lane/8 into s_rm.  Called
 // by the whole block; s_rm is complete after the caller's next barrier.
-template <bool VEC, bool HAS_D>
+template <RowLoad LD, bool HAS_D>
 __device__ __forceinline__ void chunk_masses(const Dist& d, float c2, int64_t ch, int64_t V, int t,
                                              double* s_rm) {
     static_assert(kChunk == (int64_t)kWavesPerBlock * kVecs * kWave * 8 && kPerThread == 8 * 8,
@@ -525,14 +572,12 @@ __device__ __forceinline__ void chunk_masses(const Dist& d, float c2, int64_t ch
     const int lane = t & (kWave - 1), wv = t / kWave;
     const int64_t base = ch * kChunk + (int64_t)wv * (kVecs * kWave * 8) + (int64_t)lane * 8;
     Raw rt, rd;
-    if (VEC) {
 #pragma unroll
-        for (int j = 0; j < kVecs; ++j) {
-            const int64_t e = base + (int64_t)j * kWave * 8;
-            if (e < V) {
-                rt[j] = *reinterpret_cast<const uint4*>(d.zt_row + e);
-                if (HAS_D) rd[j] = *reinterpret_cast<const uint4*>(d.zd_row + e);
-            }
+    for (int j = 0; j < kVecs; ++j) {
+        const int64_t e = base + (int64_t)j * kWave * 8;
+        if (e < V) {
+            rt[j] = load8<LD, false>(d.zt_row, e, V);
+            if (HAS_D) rd[j] = load8<LD, false>(d.zd_row, e, V);
         }
     }
 #pragma unroll
@@ -541,7 +586,7 @@ __device__ __forceinline__ void chunk_masses(const Dist& d, float c2, int64_t ch
         double m = 0.0;
         if (e < V) {
             float r[8];
-            dist8<VEC, HAS_D>(d, c2, rt[j], rd[j], e, V, r);
+            dist8<LD, HAS_D>(d, c2, rt[j], rd[j], e, V, r);
             m = (((double)r[0] + (double)r[1]) + ((double)r[2] + (double)r[3])) +
                 (((double)r[4] + (double)r[5]) + ((double)r[6] + (double)r[7]));
         }
@@ -671,7 +716,7 @@ __device__ __forceinline__ double locate_range(const double* fm, int64_t nchunk,
 // ranges of 64 elements (thread t owns range t); the last block of the
 // sequence finds the range holding u*R (locate_range), then the element
 // within the range (one lane each).
-template <bool VEC>
+template <RowLoad LD>
 __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
     __shared__ float sM[33], sZ[33];
     __shared__ double s_rm[kAThreads];
@@ -785,8 +830,8 @@ __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
     // the mass of this thread's range of chunk ch (every thread of the block calls it)
     auto mass_of = [&](int64_t ch) {
         __syncthreads();                     // s_rm's previous readers are done
-        if (d.zd_row) chunk_masses<VEC, true>(d, a.c2, ch, a.V, t, s_rm);
-        else chunk_masses<VEC, false>(d, a.c2, ch, a.V, t, s_rm);
+        if (d.zd_row) chunk_masses<LD, true>(d, a.c2, ch, a.V, t, s_rm);
+        else chunk_masses<LD, false>(d, a.c2, ch, a.V, t, s_rm);
         __syncthreads();
         return s_rm[t];
     };
@@ -946,7 +991,7 @@ __global__ __launch_bounds__(1024) void tree_greedy_kernel(AcceptArgs a) {
 // tokens zeroed: each block sums its chunk as for chains (the removed tokens
 // of a 64-element range are a bit mask), and the last block of the sequence
 // searches the chunk, the range and the element holding u[N] R.
-template <bool VEC>
+template <RowLoad LD>
 __global__ __launch_bounds__(kAThreads) void tree_sample_kernel(AcceptArgs a) {
     __shared__ float sM[kMaxTree + 1], sZ[kMaxTree + 1];
     __shared__ int s_par[kMaxTree], s_x[kMaxTree], s_path[kMaxTree], s_kill[kMaxTree];
@@ -1070,7 +1115,7 @@ __global__ __launch_bounds__(kAThreads) void tree_sample_kernel(AcceptArgs a) {
         if (e0 >= a.V) return 0.0;
         Dist dd = d;
         killed_in(e0, dd);
-        return range_mass<VEC, false>(dd, a.c2, e0, e1);
+        return range_mass<LD, false>(dd, a.c2, e0, e1);
     };
     {
         store_coherent(fm + c * kAThreads + t, mass_of(c));
@@ -1172,6 +1217,13 @@ hipError_t accept_scratch(void** ptr) {
     return hipSuccess;
 }
 
+#define SPEC_ROW_LOAD(kernel, ...)                                                 \
+    do {                                                                           \
+        if (ld == kAligned) hipLaunchKernelGGL(kernel<kAligned>, __VA_ARGS__);     \
+        else if (ld == kLoose) hipLaunchKernelGGL(kernel<kLoose>, __VA_ARGS__);    \
+        else hipLaunchKernelGGL(kernel<kShort>, __VA_ARGS__);                      \
+    } while (0)
+
 hipError_t launch_accept(const AcceptPlan& p, const uint16_t* zt, const uint16_t* zd, const int32_t* x,
                          const float* u, int64_t B, int64_t k, int64_t V, float temperature,
                          int32_t* out_tokens, int32_t* num_accepted, void* workspace, hipStream_t stream,
@@ -1186,7 +1238,7 @@ hipError_t launch_accept(const AcceptPlan& p, const uint16_t* zt, const uint16_t
     a.finem = reinterpret_cast<double*>(ws + p.fine_off);
     a.ctr = reinterpret_cast<unsigned int*>(ws + p.ctr_off);
     a.V = V; a.nchunk = p.nchunk; a.nslice = (uint32_t)p.nschunk; a.B = (int)B; a.k = (int)k;
-    const bool vec = (V % 8 == 0) && ((uintptr_t)zt % 16 == 0) && (zd == nullptr || (uintptr_t)zd % 16 == 0);
+    const RowLoad ld = row_load(V, zt, zd);
     a.rt0 = tstats ? (uint32_t)(k + 1) : 0u;
     if (temperature == 0.0f) {
         a.R = (uint32_t)(k + 1);
@@ -1196,8 +1248,7 @@ hipError_t launch_accept(const AcceptPlan& p, const uint16_t* zt, const uint16_t
         if (a.items > 0) {
             const unsigned g1 = stream_blocks(a.items, cus);
             a.sw = g1 * kWavesPerBlock;
-            if (vec) hipLaunchKernelGGL(greedy_partial_kernel<true>, dim3(g1), dim3(kAThreads), 0, stream, a);
-            else hipLaunchKernelGGL(greedy_partial_kernel<false>, dim3(g1), dim3(kAThreads), 0, stream, a);
+            SPEC_ROW_LOAD(greedy_partial_kernel, dim3(g1), dim3(kAThreads), 0, stream, a);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
@@ -1221,8 +1272,7 @@ hipError_t launch_accept(const AcceptPlan& p, const uint16_t* zt, const uint16_t
         // tokens, 64 (sequence, draft) pairs per wave
         a.zx = reinterpret_cast<float2*>(ws + p.zx_off);
         const unsigned gz = (unsigned)((B * k + kAThreads - 1) / kAThreads);
-        if (vec) hipLaunchKernelGGL(stoch_stats_kernel<true>, dim3(g1 + gz), dim3(kAThreads), 0, stream, a);
-        else hipLaunchKernelGGL(stoch_stats_kernel<false>, dim3(g1 + gz), dim3(kAThreads), 0, stream, a);
+        SPEC_ROW_LOAD(stoch_stats_kernel, dim3(g1 + gz), dim3(kAThreads), 0, stream, a);
     } else {
         hipLaunchKernelGGL(clear_tickets_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, a.ctr,
                            (int)B);
@@ -1230,8 +1280,7 @@ hipError_t launch_accept(const AcceptPlan& p, const uint16_t* zt, const uint16_t
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     dim3 g2((unsigned)p.nchunk, (unsigned)B);
-    if (vec) hipLaunchKernelGGL(stoch_sample_kernel<true>, g2, dim3(kAThreads), 0, stream, a);
-    else hipLaunchKernelGGL(stoch_sample_kernel<false>, g2, dim3(kAThreads), 0, stream, a);
+    SPEC_ROW_LOAD(stoch_sample_kernel, g2, dim3(kAThreads), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -1253,26 +1302,23 @@ hipError_t launch_accept_tree(const AcceptPlan& p, const uint16_t* zt, const int
     a.R = a.Rs = (uint32_t)(N + 1);
     a.rt0 = 0;
     a.items = (uint32_t)(B * a.Rs * p.nschunk);
-    const bool vec = (V % 8 == 0) && ((uintptr_t)zt % 16 == 0);
+    const RowLoad ld = row_load(V, zt, nullptr);
     const unsigned g1 = stream_blocks(a.items, cus);
     a.sw = g1 * kWavesPerBlock;
     if (temperature == 0.0f) {
         a.c2 = 0.0f;
-        if (vec) hipLaunchKernelGGL(greedy_partial_kernel<true>, dim3(g1), dim3(kAThreads), 0, stream, a);
-        else hipLaunchKernelGGL(greedy_partial_kernel<false>, dim3(g1), dim3(kAThreads), 0, stream, a);
+        SPEC_ROW_LOAD(greedy_partial_kernel, dim3(g1), dim3(kAThreads), 0, stream, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(tree_greedy_kernel, dim3((unsigned)B), dim3(1024), 0, stream, a);
         return hipGetLastError();
     }
     a.c2 = (float)(1.4426950408889634 / (double)temperature);
-    if (vec) hipLaunchKernelGGL(stoch_stats_kernel<true>, dim3(g1), dim3(kAThreads), 0, stream, a);
-    else hipLaunchKernelGGL(stoch_stats_kernel<false>, dim3(g1), dim3(kAThreads), 0, stream, a);
+    SPEC_ROW_LOAD(stoch_stats_kernel, dim3(g1), dim3(kAThreads), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     dim3 g2((unsigned)p.nchunk, (unsigned)B);
-    if (vec) hipLaunchKernelGGL(tree_sample_kernel<true>, g2, dim3(kAThreads), 0, stream, a);
-    else hipLaunchKernelGGL(tree_sample_kernel<false>, g2, dim3(kAThreads), 0, stream, a);
+    SPEC_ROW_LOAD(tree_sample_kernel, g2, dim3(kAThreads), 0, stream, a);
     return hipGetLastError();
 }
 
