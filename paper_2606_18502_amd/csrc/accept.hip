@@ -75,7 +75,7 @@ struct AcceptArgs {
     uint32_t ntst;         // entries per target row in tst
     float2* tsm;           // [B][k+1] tst merged to one entry per row by the statistics kernel, or null
     float2* zx;            // [B][k] (target, draft) logits at the draft tokens, gathered by the statistics
-                           // kernel for the sampling kernel (chain mode with a statistics pass), or null
+                           // kernel for the sampling kernel, or null (no statistics pass, greedy)
     uint32_t sw;           // streaming waves of the statistics grid (the first sw waves)
     double* finem;         // [B][nchunk][256] residual mass per 64-element range
     unsigned int* ctr;     // [B]
@@ -399,16 +399,12 @@ __device__ __forceinline__ void merge_ms(float& m, float& z, float om, float oz)
     }
 }
 
-// (M, Z) of the n statistics entries st[0..n) merged over one wave: lane l
-// merges entries l, l + 64, l + 128, ... in that order (`first` is its entry
-// l, loaded by the caller, or (-inf, 0) past n), then the wave combines the
-// lanes.  A row given as its single merged entry gives back that entry
-// exactly (the other lanes add zeros).
-__device__ __forceinline__ float2 merge_row_ms(const float2* st, uint32_t n, int lane, float2 first) {
+// A lane's share of a row's n statistics entries st[0..n): entries lane,
+// lane + 64, lane + 128, ... merged in that order.
+__device__ __forceinline__ float2 lane_ms(const float2* st, uint32_t n, int lane) {
     float m = -INFINITY, z = 0.0f;
-    merge_ms(m, z, first.x, first.y);
     // loads issued 8 per lane before they are merged, in entry order
-    for (int64_t q0 = lane + kWave; q0 < n; q0 += 8 * kWave) {
+    for (int64_t q0 = lane; q0 < n; q0 += 8 * kWave) {
         float2 v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
@@ -418,9 +414,60 @@ __device__ __forceinline__ float2 merge_row_ms(const float2* st, uint32_t n, int
 #pragma unroll
         for (int u = 0; u < 8; ++u) merge_ms(m, z, v[u].x, v[u].y);
     }
-    const float M = wave_max(m);
-    const float Z = wave_sum(m == -INFINITY ? 0.0f : z * exp2f(m - M));
+    return make_float2(m, z);
+}
+
+// (M, Z) of a row from the lanes' shares.  A row given as its single merged
+// entry gives back that entry exactly (the other lanes add zeros).
+__device__ __forceinline__ float2 wave_ms(float2 v) {
+    const float M = wave_max(v.x);
+    const float Z = wave_sum(v.x == -INFINITY ? 0.0f : v.y * exp2f(v.x - M));
     return make_float2(M, Z);
+}
+
+// (M, Z) of rows 0 .. rows-1 (at most ROWS) of sequence b into sM and sZ:
+// wave wv merges rows wv, wv + 4, ....  Rows of at most 64 entries (V <=
+// 262144, or merged by the statistics kernel) are all loaded before any is
+// merged, and the wave reductions of four rows, which are independent,
+// overlap.  Longer ones are merged row by row in a loop: unrolled, its code
+// alone made the kernels wait for instructions (a tree's 26 rows 4.2 us, 3.2 so).
+template <int ROWS>
+__device__ __forceinline__ void merge_rows(const AcceptArgs& a, int b, int rows, int lane, int wv, float* sM,
+                                           float* sZ) {
+    constexpr int kPer = (ROWS + kWavesPerBlock - 1) / kWavesPerBlock;
+    const bool given = a.rt0 > 0 && a.tsm == nullptr;         // target rows as the LM-head epilogue left them
+    if ((given && a.ntst > (uint32_t)kWave) || a.nslice > (uint32_t)kWave) {
+        for (int r = wv; r < rows; r += kWavesPerBlock) {
+            uint32_t n;
+            const float2* st = row_stats(a, b, r, n);
+            const float2 mz = wave_ms(lane_ms(st, n, lane));
+            if (lane == 0) { sM[r] = mz.x; sZ[r] = mz.y; }
+        }
+        return;
+    }
+    float2 v[(kPer + 3) / 4 * 4];
+#pragma unroll
+    for (int i = 0; i < (kPer + 3) / 4 * 4; ++i) {
+        const int r = wv + i * kWavesPerBlock;
+        v[i] = make_float2(-INFINITY, 0.0f);
+        if (i < kPer && r < rows) {
+            uint32_t n;
+            const float2* st = row_stats(a, b, r, n);
+            if ((uint32_t)lane < n) v[i] = st[lane];
+        }
+    }
+#pragma unroll
+    for (int i0 = 0; i0 < kPer; i0 += 4) {
+        if (wv + i0 * kWavesPerBlock >= rows) break;
+        float2 mz[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mz[i] = wave_ms(v[i0 + i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = wv + (i0 + i) * kWavesPerBlock;
+            if (lane == 0 && r < rows) { sM[r] = mz[i].x; sZ[r] = mz[i].y; }
+        }
+    }
 }
 
 template <RowLoad LD>
@@ -436,8 +483,7 @@ __global__ __launch_bounds__(kAThreads) void stoch_stats_kernel(AcceptArgs a) {
         const uint32_t rows = (uint32_t)a.B * (uint32_t)(a.k + 1);
         for (uint32_t m = GW - 1 - gw; m < rows; m += GW) {
             const float2* st = a.tst + (int64_t)m * a.ldtst;
-            const float2 first = (uint32_t)lane < a.ntst ? st[lane] : make_float2(-INFINITY, 0.0f);
-            const float2 r = merge_row_ms(st, a.ntst, lane, first);
+            const float2 r = wave_ms(lane_ms(st, a.ntst, lane));
             if (lane == 0) a.tsm[m] = r;
         }
     }
@@ -457,9 +503,11 @@ __global__ __launch_bounds__(kAThreads) void stoch_stats_kernel(AcceptArgs a) {
         if (pz < (uint32_t)a.B * (uint32_t)a.k) {
             const int32_t xg = a.x[pz];
             float gt = 0.0f, gd = 0.0f;
-            if (xg >= 0 && xg < a.V) {
-                const int64_t b = pz / (uint32_t)a.k, i = pz % (uint32_t)a.k;
-                gt = bf16_to_f32(a.zt[(b * (a.k + 1) + i) * a.V + xg]);
+            const int64_t b = pz / (uint32_t)a.k, i = pz % (uint32_t)a.k;
+            // a tree's node is scored by its parent's row
+            const int64_t row = a.parent ? (int64_t)a.parent[pz] + 1 : i;
+            if (xg >= 0 && xg < a.V && row >= 0 && row <= i) {
+                gt = bf16_to_f32(a.zt[(b * (a.k + 1) + row) * a.V + xg]);
                 if (a.zd) gd = bf16_to_f32(a.zd[(b * a.k + i) * a.V + xg]);
             }
             a.zx[pz] = make_float2(gt, gd);
@@ -484,21 +532,15 @@ struct Dist {
     float mt, inv_zt;         // merged max and 1/sum of the target row
     float md, inv_zd;
     int64_t skip;             // element forced to zero (one-hot draft), -1 if none
-    int64_t kill0;            // token tree: bit i of `kill` zeroes element kill0 + i (rejected candidates)
-    uint64_t kill;
 };
-
-__device__ __forceinline__ bool killed(const Dist& d, int64_t e) {
-    const uint64_t i = (uint64_t)(e - d.kill0);
-    return i < 64 && ((d.kill >> i) & 1ull);
-}
 
 // Probabilities of the 8 elements at e (< e1) from loaded vectors: with a
 // draft row (HAS_D) the residual max(0, p - q), else p with element `skip`
-// (the one-hot draft token, or -1) set to zero.
+// (the one-hot draft token, or -1) and the elements of the bit mask `kill` set
+// to zero.
 template <RowLoad LD, bool HAS_D>
 __device__ __forceinline__ void dist8(const Dist& d, float c2, uint4 rt, uint4 rd, int64_t e,
-                                      int64_t e1, float r[8]) {
+                                      int64_t e1, unsigned kill, float r[8]) {
     float zt[8];
     cut8<LD>(rt, e, e1, 0);
     unpack8(rt, zt);
@@ -516,7 +558,7 @@ __device__ __forceinline__ void dist8(const Dist& d, float c2, uint4 rt, uint4 r
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const float p = __builtin_amdgcn_exp2f(fmaf(zt[q], c2, -d.mt)) * d.inv_zt;
-            r[q] = (in8<LD>(e, q, e1) && e + q != d.skip && !killed(d, e + q)) ? p : 0.0f;
+            r[q] = (in8<LD>(e, q, e1) && e + q != d.skip && !((kill >> q) & 1u)) ? p : 0.0f;
         }
     }
 }
@@ -529,32 +571,8 @@ __device__ __forceinline__ float dist1(const Dist& d, float c2, int64_t e) {
         const float qq = __builtin_amdgcn_exp2f(fmaf(bf16_to_f32(d.zd_row[e]), c2, -d.md)) * d.inv_zd;
         return fmaxf(p - qq, 0.0f);
     } else {
-        return (e != d.skip && !killed(d, e)) ? p : 0.0f;
+        return e != d.skip ? p : 0.0f;
     }
-}
-
-// Mass of the range [e0, e1) of at most 64 elements (e0 < e1), in double.
-// The 8 vectors of the range are loaded before any is used.
-template <RowLoad LD, bool HAS_D>
-__device__ __forceinline__ double range_mass(const Dist& d, float c2, int64_t e0, int64_t e1) {
-    Raw rt, rd;
-#pragma unroll
-    for (int j = 0; j < kVecs; ++j) {
-        rt[j] = load8<LD, false>(d.zt_row, e0 + j * 8, e1);
-        if (HAS_D) rd[j] = load8<LD, false>(d.zd_row, e0 + j * 8, e1);
-    }
-    double m = 0.0;
-#pragma unroll
-    for (int j = 0; j < kVecs; ++j) {
-        const int64_t e = e0 + j * 8;
-        if (e < e1) {
-            float r[8];
-            dist8<LD, HAS_D>(d, c2, rt[j], rd[j], e, e1, r);
-            m += (((double)r[0] + (double)r[1]) + ((double)r[2] + (double)r[3])) +
-                 (((double)r[4] + (double)r[5]) + ((double)r[6] + (double)r[7]));
-        }
-    }
-    return m;
 }
 
 // Masses of the kAThreads ranges of kPerThread elements of chunk ch, read with
@@ -562,11 +580,13 @@ __device__ __forceinline__ double range_mass(const Dist& d, float c2, int64_t e0
 // in kVecs loads of 512 (16 bytes per lane, consecutive lanes on consecutive
 // 16-byte pieces, so one load instruction reads 1 KiB contiguous).  The 8 lanes
 // that share a range add their sums by xor exchanges in a fixed order, and the
-// first of them stores the mass of range wv*64 + j*8 + lane/8 into s_rm.  Called
-// by the whole block; s_rm is complete after the caller's next barrier.
+// first of them stores the mass of range wv*64 + j*8 + lane/8 into s_rm.  `kill`
+// (without a draft row, or null) is a bit per element of the chunk: those
+// elements have no mass.  Called by the whole block; s_rm is complete after the
+// caller's next barrier.
 template <RowLoad LD, bool HAS_D>
 __device__ __forceinline__ void chunk_masses(const Dist& d, float c2, int64_t ch, int64_t V, int t,
-                                             double* s_rm) {
+                                             double* s_rm, const uint8_t* kill) {
     static_assert(kChunk == (int64_t)kWavesPerBlock * kVecs * kWave * 8 && kPerThread == 8 * 8,
                   "a range is 8 lanes of one load");
     const int lane = t & (kWave - 1), wv = t / kWave;
@@ -586,7 +606,8 @@ __device__ __forceinline__ void chunk_masses(const Dist& d, float c2, int64_t ch
         double m = 0.0;
         if (e < V) {
             float r[8];
-            dist8<LD, HAS_D>(d, c2, rt[j], rd[j], e, V, r);
+            const unsigned kb = !HAS_D && kill ? kill[(e - ch * kChunk) / 8] : 0u;
+            dist8<LD, HAS_D>(d, c2, rt[j], rd[j], e, V, kb, r);
             m = (((double)r[0] + (double)r[1]) + ((double)r[2] + (double)r[3])) +
                 (((double)r[4] + (double)r[5]) + ((double)r[6] + (double)r[7]));
         }
@@ -595,51 +616,6 @@ __device__ __forceinline__ void chunk_masses(const Dist& d, float c2, int64_t ch
         m += __shfl_xor(m, 4);
         if ((lane & 7) == 0) s_rm[wv * (kVecs * 8) + j * 8 + (lane >> 3)] = m;
     }
-}
-
-// Block-wide scan of one double per thread, in thread order: the thread's
-// interval [lo, hi) of the running sum and the block total.  Intervals of
-// consecutive threads tile exactly (hi of thread t is bit-identical to lo of
-// thread t + 1), so a value in [0, total) has exactly one owner, and the
-// owner's own value is positive.  `sh` holds kWavesPerBlock doubles.
-__device__ __forceinline__ void block_scan_d(double v, double* sh, double& lo, double& hi, double& total) {
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-    double incl = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const double y = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += y;
-    }
-    double excl = __shfl_up(incl, 1, kWave);
-    if (lane == 0) excl = 0.0;
-    __syncthreads();                       // sh may still be read by a previous scan
-    if (lane == kWave - 1) sh[wv] = incl;
-    __syncthreads();
-    double before = 0.0;
-    for (int q = 0; q < wv; ++q) before += sh[q];
-    double tot = before;
-    for (int q = wv; q < kWavesPerBlock; ++q) tot += sh[q];
-    lo = before + excl;
-    hi = before + incl;
-    total = tot;
-}
-
-// Owner of `target` among the block's intervals (base + [lo, hi)): writes the
-// owner's index (always in [0, blockDim.x)) and base + lo to shared memory.
-// If rounding left no owner (target at or past the end), the last thread with
-// positive mass owns it; with no positive mass at all (non-finite logits),
-// thread 0 does.
-__device__ __forceinline__ void find_owner(double v, double lo, double hi, double base, double target, int* s_own,
-                                           double* s_base, int* s_lastpos) {
-    if (threadIdx.x == 0) { *s_own = -1; *s_lastpos = -1; }
-    __syncthreads();
-    const double blo = base + lo, bhi = base + hi;
-    if (blo <= target && target < bhi) { *s_own = threadIdx.x; *s_base = blo; }
-    if (v > 0.0) atomicMax(s_lastpos, (int)threadIdx.x);
-    __syncthreads();
-    const int lastpos = *s_lastpos;
-    if (*s_own < 0 && (int)threadIdx.x == (lastpos >= 0 ? lastpos : 0)) { *s_own = threadIdx.x; *s_base = blo; }
-    __syncthreads();
 }
 
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -652,64 +628,125 @@ __device__ __forceinline__ double load_coherent(const double* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-constexpr int kRunRegs = 16;   // range masses a thread keeps in registers (nchunk <= 16: V <= 262144)
-
-// The inverse-CDF search down to one 64-element range, by the whole last
-// block of a sequence in one round trip: its residual masses fm[0 .. nchunk * 256),
-// one per 64-element range in vocabulary order (range th of chunk ch at
-// ch * 256 + th, stored by every block of the sequence), are read in runs of
-// nchunk consecutive ranges per thread; the runs are summed in order and
-// scanned across the block, which gives the total R; the thread whose run
-// holds target = u * R walks it range by range.  Writes the chosen range
-// (index into fm) to *s_rng and the mass before it to *s_base; where rounding
-// leaves target past every interval, the last range with positive mass is
-// taken, and range 0 where there is none (R == 0 or not finite).  Returns R.
-__device__ __forceinline__ double locate_range(const double* fm, int64_t nchunk, float u, double* sh, int* s_own,
-                                               double* s_base, int* s_lastpos, int* s_rng) {
-    const int t = threadIdx.x;
-    const int64_t r0 = (int64_t)t * nchunk;
-    const bool in_regs = nchunk <= kRunRegs;
-    double v[kRunRegs];
-    double run = 0.0;
-    if (in_regs) {
-#pragma unroll
-        for (int i = 0; i < kRunRegs; ++i) v[i] = i < nchunk ? load_coherent(fm + r0 + i) : 0.0;
-#pragma unroll
-        for (int i = 0; i < kRunRegs; ++i) run += v[i];
-    } else {
-        for (int64_t i = 0; i < nchunk; ++i) run += load_coherent(fm + r0 + i);
-    }
-    double lo, hi, R;
-    block_scan_d(run, sh, lo, hi, R);
-    const double target = (double)u * R;
-    find_owner(run, lo, hi, 0.0, target, s_own, s_base, s_lastpos);
-    if (t == *s_own) {
-        double cum = *s_base, last_base = cum, pick_base = cum;
-        int64_t pick = -1, lastpos = -1;
-        auto visit = [&](int64_t i, double m) {
-            const double nx = cum + m;
-            if (m > 0.0) { lastpos = i; last_base = cum; }
-            if (pick < 0 && cum <= target && target < nx) { pick = i; pick_base = cum; }
-            cum = nx;
-        };
-        if (in_regs) {
-#pragma unroll
-            for (int i = 0; i < kRunRegs; ++i)
-                if (i < nchunk) visit(i, v[i]);
-        } else {
-            for (int64_t i = 0; i < nchunk; ++i) visit(i, load_coherent(fm + r0 + i));
-        }
-        if (pick < 0) {
-            pick = lastpos >= 0 ? lastpos : 0;
-            pick_base = lastpos >= 0 ? last_base : *s_base;
-        }
-        *s_rng = R > 0.0 ? (int)(r0 + pick) : 0;
-        *s_base = R > 0.0 ? pick_base : 0.0;
-    }
-    __syncthreads();
-    return R;
+// Running sums over the lanes of a wave, on DPP lane shifts: within 16-lane
+// rows, then the totals of the rows before.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+    return __hiloint2double(hi, lo);
 }
 
+__device__ __forceinline__ double wave_scan_d(double v) {
+    v += dpp_or_zero<0x111, 0xF>(v);    // row_shr 1
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);    // rows 1 and 3: the last lane of the row before
+    v += dpp_or_zero<0x143, 0xC>(v);    // rows 2 and 3: lane 31
+    return v;
+}
+
+constexpr int kRunRegs = 16;   // chunks whose masses a thread holds at a time (all of them up to V = 262144)
+
+// What the last block of a sequence shares while it searches.
+struct Search {
+    double tot[kRunRegs * kWavesPerBlock];  // mass of each wave's 64 ranges of each chunk, in vocabulary order
+    double base[kWavesPerBlock];            // of each wave that holds target: the mass before
+    int own[kWavesPerBlock];                // its range, INT_MAX where the wave does not hold target
+    int lastpos;                            // the last range with mass
+    double last_base;                       // the mass before that
+};
+static_assert(kRunRegs * kWavesPerBlock == kWave, "a wave total per lane");
+
+// The inverse-CDF search down to one 64-element range, by the whole last
+// block of a sequence: its masses fm[0 .. nchunk * 256), one per 64-element
+// range in vocabulary order (range th of chunk ch at ch * 256 + th, stored by
+// every block of the sequence), are read with consecutive threads on
+// consecutive ranges; every wave scans its 64 ranges of each chunk and then
+// (each wave for itself) the wave totals, and the range whose interval holds
+// target = u * R (R the total) is found by the lane that holds it, with no
+// search from level to level.  Intervals of consecutive ranges tile exactly:
+// each end is bit-identical to the next start.  Returns R, the chosen range and
+// the mass before it; where rounding leaves target in no interval, the last
+// range with positive mass is taken, and range 0 where there is none (R == 0 or
+// not finite).  Beyond kRunRegs chunks they are read in batches, twice (the
+// total comes first).
+//
+// Round trips and barriers bound it (all but one block of the sequence have
+// left).  V = 128256: 4.4 us with a run of consecutive ranges per thread (every
+// load of a wave on 64 lines), shuffle scans and a walk of the owner's run;
+// 3.3 us so.
+struct Range {
+    double total, before;
+    int rng;
+};
+
+__device__ __forceinline__ Range locate_range(const double* fm, int64_t nchunk, float u, Search& s) {
+    const int t = threadIdx.x, lane = t & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(t / kWave);
+    double incl[kRunRegs], pre = 0.0;
+    // running sums over this thread's wave of chunks c0 .., and over all waves' totals
+    auto scan = [&](int64_t c0) {
+        double v[kRunRegs];
+#pragma unroll
+        for (int i = 0; i < kRunRegs; ++i) v[i] = c0 + i < nchunk ? load_coherent(fm + (c0 + i) * kAThreads + t) : 0.0;
+        __syncthreads();                     // s's previous readers are done
+#pragma unroll
+        for (int i = 0; i < kRunRegs; ++i) {
+            incl[i] = 0.0;
+            if (c0 + i < nchunk) incl[i] = wave_scan_d(v[i]);
+            if (lane == kWave - 1) s.tot[i * kWavesPerBlock + wv] = incl[i];
+        }
+        __syncthreads();
+        pre = wave_scan_d(s.tot[lane]);
+    };
+    auto lane_of = [](double v, int l) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                                __builtin_amdgcn_readlane(__double2loint(v), l));
+    };
+    double R = 0.0;
+    for (int64_t c0 = 0; c0 < nchunk; c0 += kRunRegs) {
+        scan(c0);
+        R += lane_of(pre, kWave - 1);
+    }
+    const double target = (double)u * R;
+    int mine = 0x7fffffff, last = -1;        // this thread's range that holds target; its last with mass
+    double mine_base = 0.0, last_base = 0.0;
+    double sum = 0.0;
+    for (int64_t c0 = 0; c0 < nchunk; c0 += kRunRegs) {
+        if (nchunk > kRunRegs) scan(c0);
+#pragma unroll
+        for (int i = 0; i < kRunRegs; ++i) {
+            if (c0 + i < nchunk) {
+                const int w = i * kWavesPerBlock + wv;
+                const double start = w > 0 ? sum + lane_of(pre, w - 1) : sum, end = sum + lane_of(pre, w);
+                const double excl = dpp_or_zero<0x138, 0xF>(incl[i]);    // the lane before
+                const double lo = start + excl, hi = lane == kWave - 1 ? end : start + incl[i];
+                const int g = (int)((c0 + i) * kAThreads) + t;
+                if (mine == 0x7fffffff && lo <= target && target < hi) { mine = g; mine_base = lo; }
+                if (incl[i] > excl) { last = g; last_base = lo; }
+            }
+        }
+        sum += lane_of(pre, kWave - 1);
+    }
+    const int first = wave_min_i32(mine);
+    if (lane == 0) s.own[wv] = first;
+    if (mine == first && first != 0x7fffffff) s.base[wv] = mine_base;
+    if (t == 0) s.lastpos = -1;
+    __syncthreads();
+    int own = 0x7fffffff, ow = 0;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w)
+        if (s.own[w] < own) { own = s.own[w]; ow = w; }
+    if (own != 0x7fffffff) return {R, s.base[ow], own};
+    if (last >= 0) atomicMax(&s.lastpos, last);
+    __syncthreads();
+    const int pos = R > 0.0 ? s.lastpos : -1;
+    if (pos < 0) return {R, 0.0, 0};
+    if (last == pos) s.last_base = last_base;
+    __syncthreads();
+    return {R, s.last_base, pos};
+}
 
 // Sampling from the residual (or bonus) distribution of position j by inverse
 // CDF in vocabulary order: every block stores the masses of its chunk's 256
@@ -720,16 +757,14 @@ template <RowLoad LD>
 __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
     __shared__ float sM[33], sZ[33];
     __shared__ double s_rm[kAThreads];
-    __shared__ int s_acc[16], s_x[16];
-    __shared__ int s_j, s_last, s_rng;
+    __shared__ int s_x[16];
+    __shared__ int s_j, s_last;
     __shared__ float s_uk;
-    __shared__ double sh[kWavesPerBlock];
-    __shared__ int s_own, s_lastpos;
-    __shared__ double s_base;
+    __shared__ Search s_find;
     const int64_t c = blockIdx.x;
     const int b = blockIdx.y;
     const int t = threadIdx.x;
-    const int lane = t & 63, wv = t >> 6;
+    const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int k = a.k;
 
     // The operands of the accept tests are loaded first (draft id, then the
@@ -752,52 +787,27 @@ __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
         }
     }
 
-    // 1. merge the slice statistics of every row of sequence b: wave wv takes
-    //    rows wv, wv+4, ...; lanes stride over slices (the first slice of
-    //    every row is loaded up front); fixed reduction order.
-    constexpr int kRowsPerWave = (33 + kWavesPerBlock - 1) / kWavesPerBlock;   // R <= 2*16+1
-    float2 first[kRowsPerWave];
-#pragma unroll
-    for (int i = 0; i < kRowsPerWave; ++i) {
-        const int r = wv + i * kWavesPerBlock;
-        first[i] = make_float2(-INFINITY, 0.0f);
-        if (r < (int)a.R) {
-            uint32_t nst;
-            const float2* st = row_stats(a, b, r, nst);
-            if ((uint32_t)lane < nst) first[i] = st[lane];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < kRowsPerWave; ++i) {
-        const int r = wv + i * kWavesPerBlock;
-        if (r < (int)a.R) {
-            uint32_t nst;
-            const float2* st = row_stats(a, b, r, nst);
-            const float2 mz = merge_row_ms(st, nst, lane, first[i]);
-            if (lane == 0) { sM[r] = mz.x; sZ[r] = mz.y; }
-        }
-    }
+    // 1. merge the slice statistics of every row of sequence b, in a fixed order
+    merge_rows<33>(a, b, (int)a.R, lane, wv, sM, sZ);   // R <= 2*16+1
     if (t < k) s_x[t] = xi;
     if (t == k) s_uk = ui;
     __syncthreads();
 
     // 2. accept tests of the k drafts, evaluated in parallel (identical in
-    //    every block of sequence b); the first rejection j is then a scan.
+    //    every block of sequence b), one lane each: the first rejection is j.
     //    t - M is formed exactly in double (bf16 * fp32 fits in 53 bits).
-    if (t < k) {
-        double p = 0.0, q = 0.0;
-        if (xi >= 0 && xi < a.V) {
-            p = exp2((double)zx_t * (double)a.c2 - (double)sM[t]) / (double)sZ[t];
-            q = a.zd ? exp2((double)zx_d * (double)a.c2 - (double)sM[k + 1 + t]) / (double)sZ[k + 1 + t] : 1.0;
+    if (wv == 0) {
+        bool acc = true;
+        if (lane < k) {
+            double p = 0.0, q = 0.0;
+            if (xi >= 0 && xi < a.V) {
+                p = exp2((double)zx_t * (double)a.c2 - (double)sM[t]) / (double)sZ[t];
+                q = a.zd ? exp2((double)zx_d * (double)a.c2 - (double)sM[k + 1 + t]) / (double)sZ[k + 1 + t] : 1.0;
+            }
+            acc = (double)ui * q < p;
         }
-        s_acc[t] = ((double)ui * q < p) ? 1 : 0;
-    }
-    __syncthreads();
-    if (t == 0) {
-        int j = k;
-        for (int i = 0; i < k; ++i)
-            if (!s_acc[i]) { j = i; break; }
-        s_j = j;
+        const unsigned long long rej = __ballot(!acc);
+        if (lane == 0) s_j = rej ? __ffsll((long long)rej) - 1 : k;
     }
     __syncthreads();
     const int j = s_j;
@@ -810,8 +820,6 @@ __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
     d.md = 0.0f;
     d.inv_zd = 0.0f;
     d.skip = -1;
-    d.kill0 = 0;
-    d.kill = 0;
     if (j < k) {
         if (a.zd) {
             d.zd_row = a.zd + ((int64_t)b * k + j) * a.V;
@@ -830,8 +838,8 @@ __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
     // the mass of this thread's range of chunk ch (every thread of the block calls it)
     auto mass_of = [&](int64_t ch) {
         __syncthreads();                     // s_rm's previous readers are done
-        if (d.zd_row) chunk_masses<LD, true>(d, a.c2, ch, a.V, t, s_rm);
-        else chunk_masses<LD, false>(d, a.c2, ch, a.V, t, s_rm);
+        if (d.zd_row) chunk_masses<LD, true>(d, a.c2, ch, a.V, t, s_rm, nullptr);
+        else chunk_masses<LD, false>(d, a.c2, ch, a.V, t, s_rm, nullptr);
         __syncthreads();
         return s_rm[t];
     };
@@ -855,8 +863,8 @@ __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
     }
 
     // 4. last block of sequence b: the range of 64 elements holding u*R.
-    double R = locate_range(fm, a.nchunk, s_uk, sh, &s_own, &s_base, &s_lastpos, &s_rng);
-    if (!(R > 0.0)) {
+    Range at = locate_range(fm, a.nchunk, s_uk, s_find);
+    if (!(at.total > 0.0)) {
         // The residual vanished (p_j == q_j wherever it is positive): sample
         // p_j itself.  This block recomputes every range mass.
         d.zd_row = nullptr;
@@ -864,23 +872,18 @@ __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
         for (int64_t ch = 0; ch < a.nchunk; ++ch) store_coherent(fm + ch * kAThreads + t, mass_of(ch));
         wait_stores();
         __syncthreads();
-        R = locate_range(fm, a.nchunk, s_uk, sh, &s_own, &s_base, &s_lastpos, &s_rng);
+        at = locate_range(fm, a.nchunk, s_uk, s_find);
     }
-    const double target = (double)s_uk * R;
+    const double target = (double)s_uk * at.total;
 
     // Then the element within the range (wave 0, one element per lane).
     if (wv == 0) {
         int64_t e0, e1;
-        range_of(s_rng / kAThreads, s_rng % kAThreads, e0, e1);
-        const double base3 = s_base;
+        range_of(at.rng / kAThreads, at.rng % kAThreads, e0, e1);
+        const double base3 = at.before;
         const int64_t e = e0 + lane;
         const float r = e < e1 ? (d.zd_row ? dist1<true>(d, a.c2, e) : dist1<false>(d, a.c2, e)) : 0.0f;
-        double incl = (double)r;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const double y = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += y;
-        }
+        const double incl = wave_scan_d((double)r);
         double excl = __shfl_up(incl, 1, kWave);
         if (lane == 0) excl = 0.0;
         const unsigned long long own = __ballot(base3 + excl <= target && target < base3 + incl);
@@ -928,14 +931,13 @@ __device__ __forceinline__ void tree_outputs(const AcceptArgs& a, int b, const i
 // current row's argmax, until no child matches; that argmax is emitted.
 __global__ __launch_bounds__(1024) void tree_greedy_kernel(AcceptArgs a) {
     __shared__ int g[kMaxTree + 1];
-    __shared__ int s_par[kMaxTree], s_x[kMaxTree], s_path[kMaxTree];
+    __shared__ int s_x[kMaxTree], s_path[kMaxTree];
     __shared__ int s_depth, s_tok;
     const int b = blockIdx.x;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int N = a.k;
     // the tree and the first statistics entry of every row of the wave are
-    // loaded before anything waits for them (one round trip for all); the
-    // tree reaches shared memory after the merge
+    // loaded before anything waits for them (one round trip for all)
     int par = -2, xv = -1;
     if (t < N) {
         par = a.parent[(int64_t)b * N + t];
@@ -957,24 +959,22 @@ __global__ __launch_bounds__(1024) void tree_greedy_kernel(AcceptArgs a) {
         const int bi = merged_argmax(a, b, r, lane, first[i]);
         if (lane == 0) g[r] = bi;
     }
-    if (t < N) {
-        s_par[t] = par;
-        s_x[t] = xv;
-    }
+    if (t < N) s_x[t] = xv;
     __syncthreads();
-    if (t == 0) {
-        int cur = -1, depth = 0;
+    if (wv == 0) {                     // a node per lane of wave 0
+        int cur = -1, depth = 0, gv;
         for (;;) {
-            const int gv = g[cur + 1];
-            int nxt = -1;
-            for (int n = cur + 1; n < N; ++n)
-                if (s_par[n] == cur && s_x[n] == gv) { nxt = n; break; }
-            if (nxt < 0) break;
-            s_path[depth++] = nxt;
-            cur = nxt;
+            gv = __builtin_amdgcn_readfirstlane(g[cur + 1]);
+            const uint64_t hit = __ballot(par == cur && lane > cur && xv == gv);
+            if (hit == 0) break;
+            cur = __builtin_ctzll(hit);
+            if (lane == 0) s_path[depth] = cur;
+            ++depth;
         }
-        s_depth = depth;
-        s_tok = g[cur + 1];
+        if (lane == 0) {
+            s_depth = depth;
+            s_tok = gv;
+        }
     }
     __syncthreads();
     tree_outputs(a, b, s_path, s_x, s_depth, s_tok, t, blockDim.x);
@@ -989,104 +989,87 @@ __global__ __launch_bounds__(1024) void tree_greedy_kernel(AcceptArgs a) {
 // acceptance the walk moves to n, else x is removed.  Where every child is
 // rejected (or there is none) the final draw comes from P with the removed
 // tokens zeroed: each block sums its chunk as for chains (the removed tokens
-// of a 64-element range are a bit mask), and the last block of the sequence
-// searches the chunk, the range and the element holding u[N] R.
+// of the chunk are a bit mask in LDS), and the last block of the sequence
+// searches the range and the element holding u[N] R.
+//
+// A chain of latencies bounds it, so the tree lies in the lanes of wave 0 (one
+// node each, N <= 64) and a step of the walk is a ballot and a few lane reads,
+// not a scan of LDS, the candidates' logits come with the statistics in one
+// round trip, and the chunk is read with coalesced loads (64 trees of 25 nodes,
+// V = 128256: the call 88.1 us; 92.2 with a lane per 64-element range, the walk
+// in LDS and a second round trip for the logits).
 template <RowLoad LD>
 __global__ __launch_bounds__(kAThreads) void tree_sample_kernel(AcceptArgs a) {
     __shared__ float sM[kMaxTree + 1], sZ[kMaxTree + 1];
-    __shared__ int s_par[kMaxTree], s_x[kMaxTree], s_path[kMaxTree], s_kill[kMaxTree];
-    __shared__ double s_p[kMaxTree];
-    __shared__ float s_u[kMaxTree + 1];
-    __shared__ int s_f, s_depth, s_nkill, s_last, s_rng;
-    __shared__ double sh[kWavesPerBlock];
-    __shared__ int s_own, s_lastpos;
-    __shared__ double s_base;
+    __shared__ double s_rm[kAThreads];
+    __shared__ uint32_t s_kill[kChunk / 32];
+    __shared__ int s_x[kMaxTree], s_path[kMaxTree];
+    __shared__ int s_f, s_last;
+    __shared__ float s_un;
+    __shared__ Search s_find;
+    static_assert(kMaxTree <= kWave, "a node per lane of wave 0");
     const int64_t c = blockIdx.x;
     const int b = blockIdx.y;
     const int t = threadIdx.x;
-    const int lane = t & 63, wv = t >> 6;
+    const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int N = a.k;
 
     // the tree, the uniforms, the first statistics entries and the
-    // candidates' logits are loaded before anything waits for them, so their
-    // round trips overlap (the logits' addresses need the tree); they reach
-    // shared memory after the merge
+    // candidates' logits (gathered by the statistics kernel) are loaded before
+    // anything waits for them: one round trip
     int par = -2, xv = -1;
-    float uv = 0.0f;
+    float uv = 0.0f, zx = 0.0f;
     if (t < N) {
         par = a.parent[(int64_t)b * N + t];
         xv = a.x[(int64_t)b * N + t];
+        zx = a.zx[(int64_t)b * N + t].x;
     }
     if (t <= N) uv = a.u[(int64_t)b * (N + 1) + t];
-    // wave wv merges rows wv, wv+4, ...: the first entry of every one of its
-    // rows is loaded before any is merged (one round trip for all of them),
-    // then each lane merges its entries in index order
-    constexpr int kTreeRowsPerWave = (kMaxTree + 1 + kWavesPerBlock - 1) / kWavesPerBlock;
-    float2 first[kTreeRowsPerWave];
-#pragma unroll
-    for (int i = 0; i < kTreeRowsPerWave; ++i) {
-        const int r = wv + i * kWavesPerBlock;
-        first[i] = make_float2(-INFINITY, 0.0f);
-        if (r <= N) {
-            uint32_t nst;
-            const float2* st = row_stats(a, b, r, nst);
-            if ((uint32_t)lane < nst) first[i] = st[lane];
-        }
-    }
-    float zx = 0.0f;
-    bool ok = false;
-    if (t < N) {
-        ok = par >= -1 && par < t && xv >= 0 && xv < a.V;
-        if (ok) zx = bf16_to_f32(a.zt[((int64_t)b * (N + 1) + par + 1) * a.V + xv]);
-    }
-#pragma unroll
-    for (int i = 0; i < kTreeRowsPerWave; ++i) {
-        const int r = wv + i * kWavesPerBlock;
-        if (r > N) break;
-        uint32_t nst;
-        const float2* st = row_stats(a, b, r, nst);
-        const float2 mz = merge_row_ms(st, nst, lane, first[i]);
-        if (lane == 0) { sM[r] = mz.x; sZ[r] = mz.y; }
-    }
-    if (t < N) {
-        s_par[t] = par;
-        s_x[t] = xv;
-    }
-    if (t <= N) s_u[t] = uv;
+    merge_rows<kMaxTree + 1>(a, b, N + 1, lane, wv, sM, sZ);
+    const bool ok = par >= -1 && par < t && xv >= 0 && xv < a.V;
+    if (t < N) s_x[t] = xv;
+    if (t == N) s_un = uv;
+    for (int i = t; i < (int)(kChunk / 32); i += kAThreads) s_kill[i] = 0u;
     __syncthreads();
-    // every candidate's probability under its parent's row; t - M is formed
-    // exactly in double (bf16 * fp32 fits in 53 bits), as for chains
-    if (t < N) s_p[t] = ok ? exp2((double)zx * (double)a.c2 - (double)sM[par + 1]) / (double)sZ[par + 1] : 0.0;
-    __syncthreads();
-    if (t == 0) {
-        int cur = -1, depth = 0, nk = 0;
+    int depth = 0;                     // wave 0's: accepted nodes,
+    uint64_t rejected = 0;             // and the nodes whose tokens are removed
+    if (wv == 0) {
+        // every candidate's probability under its parent's row; t - M is
+        // formed exactly in double (bf16 * fp32 fits in 53 bits), as for chains
+        const double p = ok ? exp2((double)zx * (double)a.c2 - (double)sM[par + 1]) / (double)sZ[par + 1] : 0.0;
+        const int p_lo = __double2loint(p), p_hi = __double2hiint(p);
+        int cur = -1;
         for (;;) {
+            uint64_t kids = __ballot(par == cur && lane > cur);
             double S = 0.0;
             int nxt = -1;
-            nk = 0;
-            for (int n = cur + 1; n < N; ++n) {
-                if (s_par[n] != cur) continue;
-                const int x = s_x[n];
-                bool valid = x >= 0 && x < a.V;
-                for (int i = 0; i < nk && valid; ++i) valid = s_kill[i] != x;
-                const double px = valid ? s_p[n] : 0.0;
-                if ((double)s_u[n] * (1.0 - S) < px) { nxt = n; break; }
+            rejected = 0;
+            while (kids) {
+                const int n = __builtin_ctzll(kids);
+                kids &= kids - 1;
+                const int x = __builtin_amdgcn_readlane(xv, n);
+                const bool valid = x >= 0 && x < a.V && (__ballot(xv == x) & rejected) == 0;
+                const double px = valid ? __hiloint2double(__builtin_amdgcn_readlane(p_hi, n),
+                                                           __builtin_amdgcn_readlane(p_lo, n))
+                                        : 0.0;
+                const float un = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(uv), n));
+                if ((double)un * (1.0 - S) < px) { nxt = n; break; }
                 if (valid) {
-                    s_kill[nk++] = x;
+                    rejected |= 1ull << n;
                     S += px;
                 }
             }
             if (nxt < 0) break;
-            s_path[depth++] = nxt;
+            if (lane == 0) s_path[depth] = nxt;
+            ++depth;
             cur = nxt;
         }
-        s_f = cur;
-        s_depth = depth;
-        s_nkill = nk;
+        if (lane == 0) s_f = cur;
+        const int64_t off = (int64_t)xv - c * kChunk;
+        if (((rejected >> lane) & 1ull) && off >= 0 && off < kChunk) atomicOr(&s_kill[off / 32], 1u << (off % 32));
     }
     __syncthreads();
     const int f = s_f;
-    int nk = s_nkill;
 
     Dist d;
     d.zt_row = a.zt + ((int64_t)b * (N + 1) + f + 1) * a.V;
@@ -1096,29 +1079,11 @@ __global__ __launch_bounds__(kAThreads) void tree_sample_kernel(AcceptArgs a) {
     d.md = 0.0f;
     d.inv_zd = 0.0f;
     d.skip = -1;
-    auto killed_in = [&](int64_t e0, Dist& dd) {     // the removed tokens of the range [e0, e0 + 64)
-        dd.kill0 = e0;
-        dd.kill = 0;
-        for (int i = 0; i < nk; ++i) {
-            const uint64_t off = (uint64_t)((int64_t)s_kill[i] - e0);
-            if (off < 64) dd.kill |= 1ull << off;
-        }
-    };
     double* fm = a.finem + (int64_t)b * a.nchunk * kAThreads;
-    auto range_of = [&](int64_t ch, int th, int64_t& e0, int64_t& e1) {
-        e0 = ch * kChunk + (int64_t)th * kPerThread;
-        e1 = min(e0 + kPerThread, a.V);
-    };
-    auto mass_of = [&](int64_t ch) {
-        int64_t e0, e1;
-        range_of(ch, t, e0, e1);
-        if (e0 >= a.V) return 0.0;
-        Dist dd = d;
-        killed_in(e0, dd);
-        return range_mass<LD, false>(dd, a.c2, e0, e1);
-    };
     {
-        store_coherent(fm + c * kAThreads + t, mass_of(c));
+        chunk_masses<LD, false>(d, a.c2, c, a.V, t, s_rm, reinterpret_cast<const uint8_t*>(s_kill));
+        __syncthreads();
+        store_coherent(fm + c * kAThreads + t, s_rm[t]);
         wait_stores();
         __syncthreads();
         if (t == 0) {
@@ -1128,30 +1093,29 @@ __global__ __launch_bounds__(kAThreads) void tree_sample_kernel(AcceptArgs a) {
         __syncthreads();
         if (!s_last) return;
     }
-    double R = locate_range(fm, a.nchunk, s_u[N], sh, &s_own, &s_base, &s_lastpos, &s_rng);
-    if (!(R > 0.0)) {
+    Range at = locate_range(fm, a.nchunk, s_un, s_find);
+    if (!(at.total > 0.0)) {
         // the removed tokens held all the mass: draw from P itself
-        nk = 0;
-        for (int64_t ch = 0; ch < a.nchunk; ++ch) store_coherent(fm + ch * kAThreads + t, mass_of(ch));
+        rejected = 0;
+        for (int64_t ch = 0; ch < a.nchunk; ++ch) {
+            __syncthreads();                     // s_rm's previous readers are done
+            chunk_masses<LD, false>(d, a.c2, ch, a.V, t, s_rm, nullptr);
+            __syncthreads();
+            store_coherent(fm + ch * kAThreads + t, s_rm[t]);
+        }
         wait_stores();
         __syncthreads();
-        R = locate_range(fm, a.nchunk, s_u[N], sh, &s_own, &s_base, &s_lastpos, &s_rng);
+        at = locate_range(fm, a.nchunk, s_un, s_find);
     }
-    const double target = (double)s_u[N] * R;
+    const double target = (double)s_un * at.total;
     if (wv == 0) {
-        int64_t e0, e1;
-        range_of(s_rng / kAThreads, s_rng % kAThreads, e0, e1);
-        const double base3 = s_base;
-        Dist dd = d;
-        killed_in(e0, dd);
+        const int64_t e0 = (int64_t)at.rng * kPerThread, e1 = min(e0 + kPerThread, a.V);
+        const double base3 = at.before;
         const int64_t e = e0 + lane;
-        const float r = e < e1 ? dist1<false>(dd, a.c2, e) : 0.0f;
-        double incl = (double)r;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const double y = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += y;
-        }
+        float r = e < e1 ? dist1<false>(d, a.c2, e) : 0.0f;
+        for (uint64_t m = rejected; m; m &= m - 1)
+            if (e == __builtin_amdgcn_readlane(xv, __builtin_ctzll(m))) r = 0.0f;
+        const double incl = wave_scan_d((double)r);
         double excl = __shfl_up(incl, 1, kWave);
         if (lane == 0) excl = 0.0;
         const unsigned long long own = __ballot(base3 + excl <= target && target < base3 + incl);
@@ -1160,9 +1124,9 @@ __global__ __launch_bounds__(kAThreads) void tree_sample_kernel(AcceptArgs a) {
         if (own) pick = __ffsll((long long)own) - 1;
         else if (pos) pick = 63 - __builtin_clzll(pos);
         else pick = 0;
-        tree_outputs(a, b, s_path, s_x, s_depth, (int)min(e0 + pick, a.V - 1), lane, kWave);
+        tree_outputs(a, b, s_path, s_x, depth, (int)min(e0 + pick, a.V - 1), lane, kWave);
         if (lane == 0) {
-            a.num[b] = s_depth;
+            a.num[b] = depth;
             a.ctr[b] = 0u;
         }
     }
@@ -1314,7 +1278,10 @@ hipError_t launch_accept_tree(const AcceptPlan& p, const uint16_t* zt, const int
         return hipGetLastError();
     }
     a.c2 = (float)(1.4426950408889634 / (double)temperature);
-    SPEC_ROW_LOAD(stoch_stats_kernel, dim3(g1), dim3(kAThreads), 0, stream, a);
+    // the candidates' logits are gathered as the chains' are
+    a.zx = reinterpret_cast<float2*>(ws + p.zx_off);
+    const unsigned gz = (unsigned)((B * N + kAThreads - 1) / kAThreads);
+    SPEC_ROW_LOAD(stoch_stats_kernel, dim3(g1 + gz), dim3(kAThreads), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     dim3 g2((unsigned)p.nchunk, (unsigned)B);

@@ -62,3 +62,28 @@ def test_rows_on_any_boundary(V, off):
     out, num = oa.accept_greedy(zt, x)
     np.testing.assert_array_equal(host(got[0][0]), out)
     np.testing.assert_array_equal(host(got[0][1]), num)
+
+
+@pytest.mark.parametrize("V", [16384 * 16, 16384 * 16 + 5, 16384 * 33 + 64])   # one batch of chunks, the next, a third
+def test_sampling_positions_over_batches_of_chunks(V):
+    """Uniform logits of weight 2^-60 but for a few tokens of equal weight, spread
+    over the vocabulary: u picks the tokens in order, at every place of the
+    search (first and last chunk, chunk and wave edges, both sides of a batch).
+    The u lie in the middle of the tokens' intervals, so rounding cannot matter."""
+    p = need_gpu()
+    say(f"search V={V}")
+    toks = sorted({0, 63, 64, 4095, 4096, 16383, 16384, V // 2, 262143 % V, V - 65, V - 1})
+    n = len(toks)
+    z = np.full((n, 1 + 1, V), -60 * 0.6931, np.float32)
+    z[:, :, toks] = 0.0
+    zt = wl.bf16_bits_from_f32(z)
+    x = np.full((n, 1), V + 1, np.int32)                     # rejected: the sample comes from row 0
+    u = np.stack([np.full(n, 0.5), (np.arange(n) + 0.5) / n], 1).astype(np.float32)
+    t = _dev(zt, 0)
+    out, num = p.verify_accept(t, None, dev_i32(x), dev_f32(u), 1.0)
+    assert np.all(host(num) == 0)
+    np.testing.assert_array_equal(host(out)[:, 0], toks)
+    par = np.full((n, 1), -1, np.int32)
+    out, _, num = p.verify_accept_tree(t, dev_i32(par), dev_i32(x), dev_f32(u), 1.0)
+    assert np.all(host(num) == 0)
+    np.testing.assert_array_equal(host(out)[:, 0], toks)
