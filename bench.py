@@ -865,7 +865,7 @@ def read_sclk():
 
 COPY_BYTES = 256 << 20
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "gemm_gate_up_M320_N28672_K4096_traffic.md")
-GEMM_SOURCE = os.path.join(ROOT, "paper_2606_18502_amd", "csrc", "gemm.hip")
+GEMM_SOURCE = os.path.join(ROOT, "paper_2606_18502_amd", "csrc", "gemm_kernel.hpp")
 
 
 def measured_traffic():
