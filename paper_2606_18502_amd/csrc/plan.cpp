@@ -108,10 +108,11 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue, bool may_split
     GemmPlan p = best_plan(M, N, K, epilogue, may_split);
     // The logits stored with their statistics are the unsplit plain GEMM's bit
     // for bit: both walk K in the same order, so K starts are staggered only
-    // where both take the same tile.
+    // where the plain plan with K unsplit and the statistics plan take the same
+    // tile.
     if (stagger_pays(p)) {
         if (epilogue == kEpiSilu) p.krot_on = 1;
-        else p.krot_on = best_plan(M, N, K, epilogue == kEpiPlain ? kEpiStats : kEpiPlain, may_split).kind == p.kind;
+        else p.krot_on = best_plan(M, N, K, epilogue == kEpiPlain ? kEpiStats : kEpiPlain, false).kind == p.kind;
     }
     if (epilogue == kEpiPlain && p.workspace_bytes == 0 && gemm_workspace_required(M, N, K))
         p.workspace_bytes = kGemmTicketBytes;

@@ -1,0 +1,67 @@
+"""The GEMM planner on the host (no GPU): plan.cpp, api.cpp and validate.cpp
+built with g++ and test stand-ins for the kernel launchers, so that a call which
+passes every check reports SPEC_ERR_HIP instead of launching."""
+
+import collections
+import ctypes
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2606_18502_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2606_18502_amd", "csrc")
+ROCM_INCLUDE = "/opt/rocm/include"
+
+PLAIN, STATS, SILU = 0, 1, 2
+Plan = collections.namedtuple("Plan", "kind splits krot m_tiles n_tiles bn groups workspace")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    if shutil.which("g++") is None or not os.path.isdir(ROCM_INCLUDE):
+        pytest.skip("g++ or the HIP headers are not available")
+    out = str(tmp_path_factory.mktemp("plan") / "libplan.so")
+    srcs = [os.path.join(CSRC, f) for f in ("api.cpp", "validate.cpp", "plan.cpp")]
+    srcs += [os.path.join(ROOT, "tests", "hostsan", f) for f in ("launch_stubs.cpp", "plan_abi.cpp")]
+    res = subprocess.run(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                          f"-I{ROCM_INCLUDE}", f"-I{os.path.join(ROOT, 'include')}", *srcs, "-o", out],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    h = _lib.declare(ctypes.CDLL(out))
+    h.test_plan_gemm.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.c_void_p]
+    h.test_plan_gemm.restype = None
+    return h
+
+
+def plan(lib, M, N, K, epilogue=PLAIN, may_split=True):
+    out = (ctypes.c_int64 * 8)()
+    lib.test_plan_gemm(M, N, K, epilogue, int(may_split), out)
+    return Plan(*out)
+
+
+def k_starts(p, N, K):
+    """The K-step at which each column's sum starts, for columns 0, 16, 32, ...
+    (every tile is a multiple of 16 columns wide)."""
+    nk = K // 128
+    return [(c // p.bn * 7) % nk if p.krot else 0 for c in range(0, N, 16)]
+
+
+def shapes(seed, count):
+    rng = random.Random(seed)
+    for _ in range(count):
+        yield rng.randint(1, 512), 8 * rng.randint(512, 5120), 128 * rng.randint(1, 112)
+
+
+def test_statistics_and_unsplit_plain_walk_k_alike(lib):
+    """The logits stored with their statistics are the unsplit plain GEMM's bit
+    for bit: both sum every column's products in the same order."""
+    fixed = [(33, 32896, 8192), (59, 38296, 6656), (320, 128256, 4096), (8, 128256, 4096), (80, 32000, 4096)]
+    for M, V, K in fixed + list(shapes(1, 30000)):
+        s, u = plan(lib, M, V, K, STATS), plan(lib, M, V, K, PLAIN, may_split=False)
+        if s.krot or u.krot:
+            assert k_starts(s, V, K) == k_starts(u, V, K), (M, V, K, s, u)

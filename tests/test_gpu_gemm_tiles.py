@@ -154,3 +154,16 @@ def test_statistics_of_the_stored_logits(M, V, K, T):
     c2 = np.float32(1.4426950408889634 / T)
     np.testing.assert_array_equal(Mg, (zmax * np.float64(c2)).astype(np.float32))
     np.testing.assert_allclose(Zg, Z, rtol=2e-5)
+
+
+@pytest.mark.parametrize("M,V,K", [(33, 32896, 8192), (59, 38296, 6656)])
+def test_stored_logits_are_the_unsplit_plain_ones_where_the_tiles_differ(M, V, K):
+    """Wide shapes whose plain GEMM may split K: a call without a workspace
+    does not, and sums K in the order of the statistics GEMM, whatever tile
+    each takes."""
+    p = need_gpu()
+    say(f"logits M={M} V={V} K={K}")
+    a, w, sa, sw = _codes(M, V, K)
+    args = (dev_u8(a), dev_f32(sa * np.float32(0.02)), dev_u8(w), dev_f32(sw))
+    z, _ = p.gemm_logit_stats(*args, 0.7)
+    assert torch.equal(z.contiguous().view(torch.int16), p.gemm(*args).contiguous().view(torch.int16))
