@@ -84,7 +84,7 @@ struct GemmArgs {
     float c2;         // epilogue 1: t = z * c2
     int silu_inter;   // > 0: SiLU-gated output of I = silu_inter columns from W = [gate; up] (N = 2I)
     int group_m;      // > 1: tiles are ordered in groups of group_m M-tiles that walk the N-tiles together
-    int krot_on;      // 1: workgroups of different N-tiles start K at staggered steps
+    int krot_on;      // 1: blocks of columns start K at staggered steps (gemm_k_start)
 };
 
 // The kernel of a kind for an epilogue (instantiated in the gemm_k*.hip units).
@@ -790,9 +790,9 @@ __global__ __launch_bounds__(64 * kTiles[KIND].wm * kTiles[KIND].wn) void gemm_f
     // this split's K-steps (shares differ by at most one)
     const int ks0 = SPLIT ? (int)((int64_t)g.ksteps * split / g.splits) : 0;
     const int nk = (SPLIT ? (int)((int64_t)g.ksteps * (split + 1) / g.splits) : g.ksteps) - ks0;
-    // Workgroups that share an activation tile may walk K from different
-    // starting points, so they do not all request the same bytes at once.
-    const int krot = !SPLIT && g.krot_on ? (nt * 7) % nk : 0;
+    // Blocks of columns may walk K from different starting points, so that
+    // the workgroups do not all request the same K columns at once.
+    const int krot = !SPLIT && g.krot_on ? gemm_k_start(n0, nk) : 0;
 
     // The epilogue's scales, loaded straight into LDS ahead of the operands
     // (rows and columns past the edge read a valid neighbour).

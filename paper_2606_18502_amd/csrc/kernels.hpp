@@ -31,7 +31,7 @@ struct GemmPlan {
     int m_tiles, n_tiles;  // output tiles
     int splits;            // K-splits (1 = none)
     int group_m;           // > 1: tile order in groups of group_m M-tiles
-    int krot_on;           // staggered K start per N-tile
+    int krot_on;           // staggered K start per block of columns
     int64_t stat_groups;   // column groups per row of the epilogue statistics (n_tiles * waves across N)
     size_t part_off;       // byte offset of the partial tiles in the workspace (tickets before it)
     size_t workspace_bytes;

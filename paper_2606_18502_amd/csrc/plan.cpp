@@ -63,9 +63,15 @@ GemmPlan best_plan(int64_t M, int64_t N, int64_t K, int epilogue, bool may_split
 
 // A staggered K start pays where few M-tiles read many N-tiles of weights in
 // step: their row stride puts one K column of all rows on few memory channels
-// (N = 28672, K = 4096: M = 8 24.0 -> 22.4 us, M = 80 28.4 -> 27.3 us; equal
-// from N = 6144 down, where the tiles are few).
+// (cold weights, in order -> staggered: N = 28672, K = 4096 M = 8 27.7 -> 24.5
+// us, M = 80 33.7 -> 29.8, M = 160 39.0 -> 35.8; N = 12288 M = 80 18.6 -> 17.9;
+// equal from N = 6144 down, where the tiles are few).
 bool stagger_pays(const GemmPlan& p) { return p.splits == 1 && p.m_tiles <= 2 && p.n_tiles >= 192; }
+
+// Whether the plain GEMM of plan p staggers: where it pays and every tile lies
+// within one block of columns that share a start (plan.hpp), so that the order
+// in which a column's products are summed depends on the column alone.
+bool plain_staggers(const GemmPlan& p) { return stagger_pays(p) && kStaggerCols % tile_bn(p.kind) == 0; }
 
 }  // namespace
 
@@ -107,13 +113,11 @@ bool gemm_strides_fit(int kind, int64_t lda, int64_t ldw) {
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue, bool may_split) {
     GemmPlan p = best_plan(M, N, K, epilogue, may_split);
     // The logits stored with their statistics are the unsplit plain GEMM's bit
-    // for bit: both walk K in the same order, so K starts are staggered only
-    // where the plain plan with K unsplit and the statistics plan take the same
-    // tile.
-    if (stagger_pays(p)) {
-        if (epilogue == kEpiSilu) p.krot_on = 1;
-        else p.krot_on = best_plan(M, N, K, epilogue == kEpiPlain ? kEpiStats : kEpiPlain, false).kind == p.kind;
-    }
+    // for bit: they stagger where that does (every kind with statistics has
+    // tiles within one block of columns).
+    if (epilogue == kEpiSilu) p.krot_on = stagger_pays(p);
+    else if (epilogue == kEpiPlain) p.krot_on = plain_staggers(p);
+    else p.krot_on = plain_staggers(best_plan(M, N, K, kEpiPlain, false));
     if (epilogue == kEpiPlain && p.workspace_bytes == 0 && gemm_workspace_required(M, N, K))
         p.workspace_bytes = kGemmTicketBytes;
     return p;

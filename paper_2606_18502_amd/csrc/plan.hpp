@@ -63,6 +63,22 @@ constexpr int tile_waves(int k) { return kTiles[k].wm * kTiles[k].wn; }
 
 constexpr int kGemmBK = 128;   // bytes (= E4M3 elements) of K per step
 
+// Staggered K start: the tiles of a block of kStaggerCols columns start the nk
+// K-steps at the same one.  A block is a whole number of tiles of every width
+// but 224, so kinds of different widths sum a column in the same order, and
+// neighbouring narrow tiles, which an XCD runs together, share the K columns
+// they request (N = 28672, K = 4096, M = 64: 30.6 us with a start per tile,
+// 29.4, 28.3, 27.9 and 27.7 with one per 256, 384, 768 and 1536 columns; the LM
+// head at M = 320 173.5 per tile, 174.2 per 768).
+constexpr int kStaggerCols = 768;
+constexpr int gemm_k_start(int n0, int nk) { return n0 / kStaggerCols * 7 % nk; }
+constexpr bool stats_tiles_within_blocks() {
+    for (int k = 0; k < kTileKinds; ++k)
+        if ((kTiles[k].has & kHasStats) && kStaggerCols % tile_bn(k) != 0) return false;
+    return true;
+}
+static_assert(stats_tiles_within_blocks(), "statistics and plain kinds sum a column in the same order");
+
 // Split-K reduction: every wave of a split tile stores its part of the partial
 // tile in the workspace, and the last of the waves that hold the same part (an
 // atomic ticket per tile and wave) adds all of them in split order and writes

@@ -18,4 +18,7 @@ void test_plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue, int may_split
     out[7] = (int64_t)p.workspace_bytes;
 }
 
+// the K-step (of nk) at which a staggered tile with first column n0 starts
+int test_k_start(int n0, int nk) { return specfp8::gemm_k_start(n0, nk); }
+
 }  // extern "C"

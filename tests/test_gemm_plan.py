@@ -44,11 +44,10 @@ def plan(lib, M, N, K, epilogue=PLAIN, may_split=True):
     return Plan(*out)
 
 
-def k_starts(p, N, K):
+def k_starts(lib, p, N, K):
     """The K-step at which each column's sum starts, for columns 0, 16, 32, ...
     (every tile is a multiple of 16 columns wide)."""
-    nk = K // 128
-    return [(c // p.bn * 7) % nk if p.krot else 0 for c in range(0, N, 16)]
+    return [lib.test_k_start(c // p.bn * p.bn, K // 128) if p.krot else 0 for c in range(0, N, 16)]
 
 
 def shapes(seed, count):
@@ -64,4 +63,19 @@ def test_statistics_and_unsplit_plain_walk_k_alike(lib):
     for M, V, K in fixed + list(shapes(1, 30000)):
         s, u = plan(lib, M, V, K, STATS), plan(lib, M, V, K, PLAIN, may_split=False)
         if s.krot or u.krot:
-            assert k_starts(s, V, K) == k_starts(u, V, K), (M, V, K, s, u)
+            assert k_starts(lib, s, V, K) == k_starts(lib, u, V, K), (M, V, K, s, u)
+
+
+@pytest.mark.parametrize("N", [12288, 14336, 16384, 24576, 28672])
+def test_wide_decode_linears_stagger(lib, N):
+    """One or two M-tiles that read 192 or more N-tiles start K at staggered
+    steps, whether or not their tile kind has a statistics epilogue."""
+    seen = set()
+    for M in range(1, 321):
+        p = plan(lib, M, N, 4096)
+        if p.splits == 1 and p.m_tiles <= 2 and p.n_tiles >= 192 and p.bn != 224:
+            assert p.krot == 1, (M, N, p)
+            seen.add(p.kind)
+    assert len(seen) >= (2 if N < 28672 else 4), seen
+    assert plan(lib, 8, 28672, 4096).krot == 1 and plan(lib, 80, 28672, 4096).krot == 1
+    assert plan(lib, 80, 6144, 4096).krot == 0
