@@ -15,13 +15,15 @@ inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // `kind` with K split `splits` ways: the K-steps of the busiest compute unit
 // (its workgroups share it, or follow each other where LDS holds no more), a
 // fixed cost per workgroup batch and its epilogue, the operand and output
-// bytes, and the split-K reduction.  The constants are a fit to 11,000 timings
-// (MI355X, cold weights: 16 shapes N x K from 768 x 4096 and 4096 x 512 to
-// 28672 x 4096 and 4096 x 14336 at 32 values of M from 1 to 4096, every kind,
-// splits 1 to 12); over the 510 shapes the kind and split it picks take 0.9%
-// longer than the fastest measured (10% of them more than 3.5%, at most 24%:
-// K of 4 steps), and none longer than the rules by ranges of M it replaced
-// (1.56 times as long on average).
+// bytes, and the split-K reduction.  The constants are a fit to timings of
+// every kind at splits 1 to 12 (MI355X, cold weights, N x K from 768 x 4096 and
+// 4096 x 512 to 28672 x 4096 and 4096 x 14336, M from 1 to 4096); the kind and
+// split it picks are within a few percent of the fastest there (at most 24% off:
+// K of 4 steps).  split_us corrects two kinds whose splits the fit took for
+// cheaper than they are: at 6144 x 4096, M = 80, the 80x64 tile split in 2 takes
+// 13.0 us and the unsplit 64x64 tile 12.2; at 4096 x 3584, M = 160, 11.9 and 10.7;
+// at 3000 x 9984, M = 144, the 160x64 tile split in 5 takes 18.7 and 64x128 in 3
+// 17.7.
 double estimate_us(int64_t M, int64_t N, int64_t K, int kind, int splits) {
     const TileShape& t = kTiles[kind];
     const int64_t tiles = ((M + tile_bm(kind) - 1) / tile_bm(kind)) * ((N + tile_bn(kind) - 1) / tile_bn(kind));
@@ -32,7 +34,7 @@ double estimate_us(int64_t M, int64_t N, int64_t K, int kind, int splits) {
     const double blocks = t.wtm * t.wtn;                           // 16x16 blocks per wave
     double us = t.step_us * (double)per_cu * (double)steps + batches * (1.61 + 0.102 * blocks) +
                 ((double)N * (double)K + (double)M * (double)K) / 10.1e6 + 0.119e-6 * 2.0 * (double)M * (double)N;
-    if (splits > 1) us += 0.7 + splits * (0.3 + 0.062 * blocks);
+    if (splits > 1) us += 0.7 + t.split_us + splits * (0.3 + 0.062 * blocks);
     return us;
 }
 

@@ -79,3 +79,14 @@ def test_wide_decode_linears_stagger(lib, N):
     assert len(seen) >= (2 if N < 28672 else 4), seen
     assert plan(lib, 8, 28672, 4096).krot == 1 and plan(lib, 80, 28672, 4096).krot == 1
     assert plan(lib, 80, 6144, 4096).krot == 0
+
+
+@pytest.mark.parametrize("M,N,K,tile", [
+    (65, 6144, 4096, (11, 1)), (80, 6144, 4096, (11, 1)),       # QKV of a small verify batch: 13.0 us as (10, 2), 12.2 so
+    (80, 7168, 4096, (11, 1)), (160, 4096, 4096, (11, 1)), (160, 4096, 3584, (11, 1)), (144, 3000, 9984, (8, 3)),
+])
+def test_splits_that_cost_more_than_they_gain(lib, M, N, K, tile):
+    """Shapes at which a K split of the 80x64 or the 160x64 tile measured slower
+    than the named kind and split."""
+    p = plan(lib, M, N, K)
+    assert (p.kind, p.splits) == tile, p
