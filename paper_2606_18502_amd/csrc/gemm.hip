@@ -61,7 +61,13 @@ hipError_t launch_gemm(const GemmPlan& p, const uint8_t* a, int64_t lda, const f
                        hipStream_t stream, int stats_mode, float c2, float2* stats, int64_t ld_stats,
                        int64_t silu_inter) {
     const bool far = !gemm_strides_fit(p.kind, lda, ldw);
-    const GemmPlan q = far ? plan_gemm_as(M, N, K, kFarKind, 1, kEpiPlain) : p;
+    GemmPlan q = p;
+    if (far) {
+        // K in the order the plan's kernel would walk it unsplit: what a call
+        // stores does not depend on its strides
+        q = plan_gemm_as(M, N, K, kFarKind, 1, kEpiPlain);
+        q.krot_on = (p.splits > 1 ? plan_gemm(M, N, K, kEpiPlain, false) : p).krot_on;
+    }
     GemmArgs g{};
     g.stats = stats; g.ld_stats = ld_stats; g.c2 = c2;
     g.silu_inter = (int)silu_inter;

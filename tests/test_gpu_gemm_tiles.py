@@ -167,3 +167,19 @@ def test_stored_logits_are_the_unsplit_plain_ones_where_the_tiles_differ(M, V, K
     args = (dev_u8(a), dev_f32(sa * np.float32(0.02)), dev_u8(w), dev_f32(sw))
     z, _ = p.gemm_logit_stats(*args, 0.7)
     assert torch.equal(z.contiguous().view(torch.int16), p.gemm(*args).contiguous().view(torch.int16))
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 28672, 512), (33, 12352, 1024)])
+def test_far_rows_of_staggered_shapes(M, N, K):
+    """Wide shapes that start K at staggered steps: rows of one tile more than
+    4 GiB apart give the bits that packed rows give."""
+    p = need_gpu()
+    say(f"far rows staggered M={M} N={N} K={K}")
+    a, w, sa, sw = _codes(M, N, K)
+    da, dw, dsa, dsw = dev_u8(a), dev_u8(w), dev_f32(sa * np.float32(0.02)), dev_f32(sw)
+    fa = _far(da, 140_000_000)
+    assert torch.equal(p.gemm(fa, dsa, dw, dsw, out_dtype=torch.float32), p.gemm(da, dsa, dw, dsw, out_dtype=torch.float32))
+    lf, sf = p.gemm_logit_stats(fa, dsa, dw, dsw, 0.0)
+    lp, sp = p.gemm_logit_stats(da, dsa, dw, dsw, 0.0)
+    assert torch.equal(lf.contiguous().view(torch.int16), lp.contiguous().view(torch.int16))
+    assert torch.equal(sf.contiguous().view(torch.int32), sp.contiguous().view(torch.int32))
