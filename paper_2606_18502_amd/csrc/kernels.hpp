@@ -51,6 +51,12 @@ GemmPlan plan_gemm_as(int64_t M, int64_t N, int64_t K, int kind, int splits, int
 // lda + 128 and (BN - 1) ldw + 128 <= 2^32).  launch_gemm takes a slower kernel
 // for longer strides.
 bool gemm_strides_fit(int kind, int64_t lda, int64_t ldw);
+// LM heads that refuse strides which the 160 x 384 tile cannot address, as the
+// interface states them: 80 < M <= 320, a wide V, an even number of K-steps, and
+// that tile streams fewer operand rows per compute unit (BM + BN rows per round
+// of 256 tiles) than 160 x 224 and, where 192 divides V, 160 x 192 do.  Every
+// other call takes any stride.
+bool lm_head_strides_limited(int64_t M, int64_t V, int64_t K);
 // stats_mode 0: plain GEMM; 1/2: also the per-(row, column group) statistics
 // of the bf16 output (softmax in base 2 with c2 = log2(e)/T, or argmax) into
 // stats [M][ld_stats]; requires p.splits == 1.

@@ -112,6 +112,12 @@ bool gemm_strides_fit(int kind, int64_t lda, int64_t ldw) {
            (uint64_t)(tile_bn(kind) - 1) * (uint64_t)ldw + kGemmBK <= lim;
 }
 
+bool lm_head_strides_limited(int64_t M, int64_t V, int64_t K) {
+    if (M <= 80 || M > 320 || V < 12288 || K / kGemmBK % 2 != 0) return false;
+    auto rows = [&](int64_t bn) { return ((M + 159) / 160 * ((V + bn - 1) / bn) + 255) / 256 * (160 + bn); };
+    return rows(384) < rows(224) && (V % 192 != 0 || rows(384) < rows(192));
+}
+
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue, bool may_split) {
     GemmPlan p = best_plan(M, N, K, epilogue, may_split);
     // The logits stored with their statistics are the unsplit plain GEMM's bit

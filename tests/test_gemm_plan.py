@@ -90,3 +90,29 @@ def test_splits_that_cost_more_than_they_gain(lib, M, N, K, tile):
     than the named kind and split."""
     p = plan(lib, M, N, K)
     assert (p.kind, p.splits) == tile, p
+
+
+HIP, UNSUPPORTED = 7, 3
+
+
+def logit_stats_status(lib, M, V, K, lda, ldw):
+    """The status of a call whose pointers are never followed (stand-in launchers)."""
+    A, ld = 0x1000, (V + 7) // 8 * 8
+    return lib.spec_fp8_gemm_logit_stats(A, lda, A, 0, A, ldw, A, 0, M, V, K, ctypes.c_float(0.7), A, ld, A,
+                                         lib.spec_logit_stats_count(M, V, K), None)
+
+
+@pytest.mark.parametrize("M,V,K,limited", [
+    (320, 128256, 4096, True), (310, 128200, 4096, True), (320, 32064, 4096, True), (300, 32008, 256, True),
+    (71, 66200, 4096, False),                  # M <= 80 (the planner takes 160 x 384 all the same)
+    (100, 128256, 4096, False), (321, 128256, 4096, False), (1000, 128256, 4096, False), (320, 128256, 4224, False), (320, 12000, 4096, False),
+    (320, 28672, 4096, False),                 # 160 x 224 tiles stream no more rows
+])
+def test_long_strides_of_the_lm_head(lib, M, V, K, limited):
+    """Strides past a tile's 4 GiB are refused for the stated shapes only, and
+    do not depend on the tile that the estimate picks."""
+    lda, ldw = ((1 << 32) - 128) // 159 // 16 * 16, ((1 << 32) - 128) // 383 // 16 * 16
+    want = UNSUPPORTED if limited else HIP
+    assert logit_stats_status(lib, M, V, K, lda, ldw) == HIP             # the longest that the tile addresses
+    assert logit_stats_status(lib, M, V, K, lda + 16, K) == want
+    assert logit_stats_status(lib, M, V, K, K, ldw + 16) == want

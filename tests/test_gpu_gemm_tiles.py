@@ -183,3 +183,22 @@ def test_far_rows_of_staggered_shapes(M, N, K):
     lp, sp = p.gemm_logit_stats(da, dsa, dw, dsw, 0.0)
     assert torch.equal(lf.contiguous().view(torch.int16), lp.contiguous().view(torch.int16))
     assert torch.equal(sf.contiguous().view(torch.int32), sp.contiguous().view(torch.int32))
+
+
+@pytest.mark.parametrize("T", [0.7, 0.0])
+def test_far_rows_of_the_wide_lm_head_tile(T):
+    """A shape on the 160x384 tile whose interface does not limit the strides:
+    activation rows further apart than that tile addresses."""
+    p = need_gpu()
+    M, V, K, lda = 71, 66200, 512, 28_000_000
+    say(f"far LM head M={M} V={V} K={K} T={T}")
+    a, w, sa, sw = _codes(M, V, K)
+    da, dw, dsa, dsw = dev_u8(a), dev_u8(w), dev_f32(sa * np.float32(0.02)), dev_f32(sw)
+    lf, sf = p.gemm_logit_stats(_far(da, lda), dsa, dw, dsw, T)
+    lp, sp = p.gemm_logit_stats(da, dsa, dw, dsw, T)
+    assert torch.equal(lf.contiguous().view(torch.int16), lp.contiguous().view(torch.int16))
+    assert torch.equal(sf[..., 0], sp[..., 0])
+    if T == 0.0:
+        assert torch.equal(sf.contiguous().view(torch.int32), sp.contiguous().view(torch.int32))
+    else:
+        torch.testing.assert_close(sf[..., 1], sp[..., 1], rtol=2e-5, atol=0)
