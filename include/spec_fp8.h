@@ -202,12 +202,14 @@ spec_status spec_fp8_kv_cache_write(const void* k, int64_t ld_k, const void* v, 
  *         and every call leaves them zero again, so one workspace serves every
  *         later call of any shape.  The rest of it is overwritten.  Calls that
  *         share a workspace must not overlap (one stream, or serialized).
- *         It is required (SPEC_ERR_WORKSPACE, SPEC_ERR_ALIGN otherwise) for
- *         the decode-sized projections: N < 12288 and either M <= 80, K >= 2048
+ *         For the decode-sized projections (N < 12288 and either M <= 80, K >= 2048
  *         and ceil(M/64)*ceil(N/64) <= 128, or 80 < M <= 320, K >= 256 and
- *         (N <= 4096 or K >= 2N).  For other shapes with a nonzero size a call
+ *         (N <= 4096 or K >= 2N)) a size is always reported, and where K is split
+ *         the workspace is required (SPEC_ERR_WORKSPACE, SPEC_ERR_ALIGN
+ *         otherwise).  For other shapes with a nonzero size a call
  *         without a usable workspace runs with K unsplit (slower, and its fp32
- *         summation order differs).
+ *         summation order differs).  Where K is not split the workspace is not
+ *         looked at.
  * Requirements: M >= 0 (0 is a no-op), N > 0, K > 0, K % 128 == 0 (else
  * SPEC_ERR_UNSUPPORTED); lda % 16 == 0, ldw % 16 == 0, A and W 16-byte
  * aligned; ldy % 8 == 0 and Y 16-byte aligned.  M and N need not be tile

@@ -81,7 +81,7 @@ spec_status spec_fp8_gemm(const uint8_t* a, int64_t lda, const float* a_scale, s
     if (st != SPEC_OK || M == 0) return st;
     specfp8::GemmPlan plan = specfp8::plan_gemm(M, N, K);
     if (!grid_fits(plan)) return SPEC_ERR_UNSUPPORTED;
-    if (plan.workspace_bytes > 0) {
+    if (plan.splits > 1) {
         const bool enough = workspace && workspace_bytes >= plan.workspace_bytes;
         const bool aligned = (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
         if (!enough || !aligned) {

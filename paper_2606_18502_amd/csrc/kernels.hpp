@@ -40,8 +40,9 @@ struct GemmPlan {
 // SiLU-gated output; the last two keep one workgroup per output tile.
 enum GemmEpilogue { kEpiPlain = 0, kEpiStats = 1, kEpiSilu = 2 };
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int epilogue = kEpiPlain, bool may_split = true);
-// Decode-sized projections, for which the caller has to bring a workspace even
-// where the plan would do without; elsewhere K is split only if there is one.
+// Decode-sized projections: a workspace size is always reported for them, and
+// where K is split a call without one is refused.  Elsewhere K is split only if
+// there is a workspace.  An unsplit plan never looks at it.
 bool gemm_workspace_required(int64_t M, int64_t N, int64_t K);
 // The plan for an explicit tile kind and K split (plan_gemm's choices are
 // made through it; also used to compare configurations).

@@ -87,6 +87,11 @@ def gemm(a: torch.Tensor, sa: torch.Tensor, w: torch.Tensor, sw: torch.Tensor,
 
     a: uint8 E4M3 [M,K]; sa: fp32 [M] (per token) or [1] (per tensor);
     w: uint8 E4M3 [N,K]; sw: fp32 [N] (per channel) or [1].
+    workspace: gemm_workspace_bytes(M, N, K) bytes on the GPU, 16-byte aligned,
+    zero-filled once and then kept for all calls of a stream.  Bring one: without it
+    (or with one too small) a decode-sized projection that splits K gets a new
+    zero-filled one in every call, and any other shape runs with K unsplit, which is
+    slower and sums in another order.
     """
     f32 = True if out_dtype is torch.float32 else (False if out_dtype is torch.bfloat16 else None)
     return (_bind or _load_bind()).gemm(a, sa, w, sw, f32, out, workspace)

@@ -75,3 +75,19 @@ def test_given_outputs_come_back_and_streams_are_followed():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref_q) and torch.equal(scales, ref_s)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(320, 4096, 4096), (80, 6144, 4096)])
+def test_an_unsplit_gemm_allocates_nothing_but_its_output(M, N, K):
+    """Decode-sized projections whose K is not split: no workspace is made."""
+    need_gpu()
+    q, s = p.quantize(torch.randn((M, K), device="cuda").to(torch.bfloat16))
+    w, sw = p.quantize(torch.randn((N, K), device="cuda").to(torch.bfloat16))
+    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    made = lambda: torch.cuda.memory_stats()["allocation.all.allocated"]
+    before = made()
+    p.gemm(q, s, w, sw, out=out)
+    assert made() == before
+    y = p.gemm(q, s, w, sw)
+    assert made() == before + 1 and torch.equal(y, out)

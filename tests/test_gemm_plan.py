@@ -92,7 +92,7 @@ def test_splits_that_cost_more_than_they_gain(lib, M, N, K, tile):
     assert (p.kind, p.splits) == tile, p
 
 
-HIP, UNSUPPORTED = 7, 3
+HIP, UNSUPPORTED, WORKSPACE, ALIGN = 7, 3, 6, 5
 
 
 def logit_stats_status(lib, M, V, K, lda, ldw):
@@ -116,3 +116,30 @@ def test_long_strides_of_the_lm_head(lib, M, V, K, limited):
     assert logit_stats_status(lib, M, V, K, lda, ldw) == HIP             # the longest that the tile addresses
     assert logit_stats_status(lib, M, V, K, lda + 16, K) == want
     assert logit_stats_status(lib, M, V, K, K, ldw + 16) == want
+
+
+def gemm_status(lib, M, N, K, ws=None, nbytes=0):
+    A = 0x1000
+    return lib.spec_fp8_gemm(A, K, A, 0, A, K, A, 0, M, N, K, A, (N + 7) // 8 * 8, 0, ws, nbytes, None)
+
+
+def test_a_workspace_is_required_where_k_is_split(lib):
+    """Decode-sized projections always report a size; only a call that splits
+    K is refused without one, and an unsplit one never looks at it."""
+    seen = collections.Counter()
+    decode = [(M, N, K) for M in (1, 8, 64, 80, 81, 128, 200, 320) for N, K in
+              ((6144, 4096), (4096, 4096), (4096, 14336), (1024, 4096), (4096, 1024), (2048, 8192))]
+    for M, N, K in decode + [(640, 4096, 14336), (1000, 4096, 14336)]:
+        required = N < 12288 and ((M <= 80 and K >= 2048 and -(-M // 64) * -(-N // 64) <= 128)
+                                  or (80 < M <= 320 and K >= 256 and (N <= 4096 or K >= 2 * N)))
+        p = plan(lib, M, N, K)
+        need = lib.spec_fp8_gemm_workspace_bytes(M, N, K)
+        if required:
+            assert need > 0, (M, N, K)
+        refused = required and p.splits > 1
+        assert gemm_status(lib, M, N, K) == (WORKSPACE if refused else HIP), (M, N, K, p)
+        assert gemm_status(lib, M, N, K, 0x1000, max(need, 1) - 1) == (WORKSPACE if refused else HIP)
+        assert gemm_status(lib, M, N, K, 0x1008, need) == (ALIGN if refused else HIP)
+        seen[required, p.splits > 1] += 1
+    assert seen[True, True] and seen[True, False] and seen[False, True]
+    assert plan(lib, 320, 4096, 4096).splits == 1 and lib.spec_fp8_gemm_workspace_bytes(320, 4096, 4096) > 0
