@@ -652,10 +652,8 @@ constexpr int kRunRegs = 16;   // chunks whose masses a thread holds at a time (
 // What the last block of a sequence shares while it searches.
 struct Search {
     double tot[kRunRegs * kWavesPerBlock];  // mass of each wave's 64 ranges of each chunk, in vocabulary order
-    double base[kWavesPerBlock];            // of each wave that holds target: the mass before
-    int own[kWavesPerBlock];                // its range, INT_MAX where the wave does not hold target
-    int lastpos;                            // the last range with mass
-    double last_base;                       // the mass before that
+    double base[kWavesPerBlock];            // the mass before each wave's candidate
+    int own[kWavesPerBlock];                // the candidate range, -1 where the wave has none
 };
 static_assert(kRunRegs * kWavesPerBlock == kWave, "a wave total per lane");
 
@@ -664,13 +662,14 @@ static_assert(kRunRegs * kWavesPerBlock == kWave, "a wave total per lane");
 // range in vocabulary order (range th of chunk ch at ch * 256 + th, stored by
 // every block of the sequence), are read with consecutive threads on
 // consecutive ranges; every wave scans its 64 ranges of each chunk and then
-// (each wave for itself) the wave totals, and the range whose interval holds
-// target = u * R (R the total) is found by the lane that holds it, with no
-// search from level to level.  Intervals of consecutive ranges tile exactly:
-// each end is bit-identical to the next start.  Returns R, the chosen range and
-// the mass before it; where rounding leaves target in no interval, the last
-// range with positive mass is taken, and range 0 where there is none (R == 0 or
-// not finite).  Beyond kRunRegs chunks they are read in batches, twice (the
+// (each wave for itself) the wave totals, with no search from level to level.
+// Returns R (the total), the last range with mass whose preceding mass is at
+// most target = u * R, and that mass; range 0 where there is none (R == 0 or
+// not finite).  The scans add in different orders, so the mass before a range
+// and the end of the one before it may differ in the last bits: an interval
+// test could leave target to a range without mass, or to none.  This rule
+// always takes a range with mass when R > 0: nothing but zeros lies before the
+// first of them.  Beyond kRunRegs chunks they are read in batches, twice (the
 // total comes first).
 //
 // Round trips and barriers bound it (all but one block of the sequence have
@@ -685,15 +684,18 @@ struct Range {
 __device__ __forceinline__ Range locate_range(const double* fm, int64_t nchunk, float u, Search& s) {
     const int t = threadIdx.x, lane = t & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(t / kWave);
     double incl[kRunRegs], pre = 0.0;
+    unsigned mass = 0;                       // bit i: this thread's range of chunk c0 + i has mass
     // running sums over this thread's wave of chunks c0 .., and over all waves' totals
     auto scan = [&](int64_t c0) {
         double v[kRunRegs];
 #pragma unroll
         for (int i = 0; i < kRunRegs; ++i) v[i] = c0 + i < nchunk ? load_coherent(fm + (c0 + i) * kAThreads + t) : 0.0;
         __syncthreads();                     // s's previous readers are done
+        mass = 0;
 #pragma unroll
         for (int i = 0; i < kRunRegs; ++i) {
             incl[i] = 0.0;
+            mass |= (v[i] > 0.0 ? 1u : 0u) << i;
             if (c0 + i < nchunk) incl[i] = wave_scan_d(v[i]);
             if (lane == kWave - 1) s.tot[i * kWavesPerBlock + wv] = incl[i];
         }
@@ -710,8 +712,8 @@ __device__ __forceinline__ Range locate_range(const double* fm, int64_t nchunk, 
         R += lane_of(pre, kWave - 1);
     }
     const double target = (double)u * R;
-    int mine = 0x7fffffff, last = -1;        // this thread's range that holds target; its last with mass
-    double mine_base = 0.0, last_base = 0.0;
+    int mine = -1;                           // this thread's last range with mass that starts by target
+    double mine_base = 0.0;
     double sum = 0.0;
     for (int64_t c0 = 0; c0 < nchunk; c0 += kRunRegs) {
         if (nchunk > kRunRegs) scan(c0);
@@ -719,33 +721,38 @@ __device__ __forceinline__ Range locate_range(const double* fm, int64_t nchunk, 
         for (int i = 0; i < kRunRegs; ++i) {
             if (c0 + i < nchunk) {
                 const int w = i * kWavesPerBlock + wv;
-                const double start = w > 0 ? sum + lane_of(pre, w - 1) : sum, end = sum + lane_of(pre, w);
-                const double excl = dpp_or_zero<0x138, 0xF>(incl[i]);    // the lane before
-                const double lo = start + excl, hi = lane == kWave - 1 ? end : start + incl[i];
-                const int g = (int)((c0 + i) * kAThreads) + t;
-                if (mine == 0x7fffffff && lo <= target && target < hi) { mine = g; mine_base = lo; }
-                if (incl[i] > excl) { last = g; last_base = lo; }
+                const double start = w > 0 ? sum + lane_of(pre, w - 1) : sum;
+                const double lo = start + dpp_or_zero<0x138, 0xF>(incl[i]);    // (the lane before)
+                if (((mass >> i) & 1u) && lo <= target) {
+                    mine = (int)((c0 + i) * kAThreads) + t;
+                    mine_base = lo;
+                }
             }
         }
         sum += lane_of(pre, kWave - 1);
     }
-    const int first = wave_min_i32(mine);
-    if (lane == 0) s.own[wv] = first;
-    if (mine == first && first != 0x7fffffff) s.base[wv] = mine_base;
-    if (t == 0) s.lastpos = -1;
+    const int last = wave_max_i32(mine);
+    if (lane == 0) s.own[wv] = last;
+    if (mine == last && last >= 0) s.base[wv] = mine_base;
     __syncthreads();
-    int own = 0x7fffffff, ow = 0;
+    int own = -1, ow = 0;
 #pragma unroll
     for (int w = 0; w < kWavesPerBlock; ++w)
-        if (s.own[w] < own) { own = s.own[w]; ow = w; }
-    if (own != 0x7fffffff) return {R, s.base[ow], own};
-    if (last >= 0) atomicMax(&s.lastpos, last);
-    __syncthreads();
-    const int pos = R > 0.0 ? s.lastpos : -1;
-    if (pos < 0) return {R, 0.0, 0};
-    if (last == pos) s.last_base = last_base;
-    __syncthreads();
-    return {R, s.last_base, pos};
+        if (s.own[w] > own) { own = s.own[w]; ow = w; }
+    if (own < 0) return {R, 0.0, 0};
+    return {R, s.base[ow], own};
+}
+
+// The element to take within the found range, one per lane of wave 0 (all 64
+// active): the last one with mass r whose preceding mass is at most target, by
+// the same rule (the last with mass, or lane 0, where there is none).
+__device__ __forceinline__ int pick_element(float r, double before, double target) {
+    const double incl = wave_scan_d((double)r);
+    const double excl = dpp_or_zero<0x138, 0xF>(incl);       // the lane before
+    const unsigned long long own = __ballot(r > 0.0f && before + excl <= target);
+    const unsigned long long pos = __ballot(r > 0.0f);
+    const unsigned long long from = own ? own : pos;
+    return from ? 63 - __builtin_clzll(from) : 0;
 }
 
 // Sampling from the residual (or bonus) distribution of position j by inverse
@@ -880,18 +887,9 @@ __global__ __launch_bounds__(kAThreads) void stoch_sample_kernel(AcceptArgs a) {
     if (wv == 0) {
         int64_t e0, e1;
         range_of(at.rng / kAThreads, at.rng % kAThreads, e0, e1);
-        const double base3 = at.before;
         const int64_t e = e0 + lane;
         const float r = e < e1 ? (d.zd_row ? dist1<true>(d, a.c2, e) : dist1<false>(d, a.c2, e)) : 0.0f;
-        const double incl = wave_scan_d((double)r);
-        double excl = __shfl_up(incl, 1, kWave);
-        if (lane == 0) excl = 0.0;
-        const unsigned long long own = __ballot(base3 + excl <= target && target < base3 + incl);
-        const unsigned long long pos = __ballot(r > 0.0f);
-        int pick;
-        if (own) pick = __ffsll((long long)own) - 1;
-        else if (pos) pick = 63 - __builtin_clzll(pos);          // rounding: last positive element
-        else pick = 0;
+        const int pick = pick_element(r, at.before, target);
         if (lane <= k) {
             int32_t* out = a.out + (int64_t)b * (k + 1);
             out[lane] = lane < j ? s_x[lane] : (lane == j ? (int)min(e0 + pick, a.V - 1) : -1);
@@ -1110,20 +1108,11 @@ __global__ __launch_bounds__(kAThreads) void tree_sample_kernel(AcceptArgs a) {
     const double target = (double)s_un * at.total;
     if (wv == 0) {
         const int64_t e0 = (int64_t)at.rng * kPerThread, e1 = min(e0 + kPerThread, a.V);
-        const double base3 = at.before;
         const int64_t e = e0 + lane;
         float r = e < e1 ? dist1<false>(d, a.c2, e) : 0.0f;
         for (uint64_t m = rejected; m; m &= m - 1)
             if (e == __builtin_amdgcn_readlane(xv, __builtin_ctzll(m))) r = 0.0f;
-        const double incl = wave_scan_d((double)r);
-        double excl = __shfl_up(incl, 1, kWave);
-        if (lane == 0) excl = 0.0;
-        const unsigned long long own = __ballot(base3 + excl <= target && target < base3 + incl);
-        const unsigned long long pos = __ballot(r > 0.0f);
-        int pick;
-        if (own) pick = __ffsll((long long)own) - 1;
-        else if (pos) pick = 63 - __builtin_clzll(pos);
-        else pick = 0;
+        const int pick = pick_element(r, at.before, target);
         tree_outputs(a, b, s_path, s_x, depth, (int)min(e0 + pick, a.V - 1), lane, kWave);
         if (lane == 0) {
             a.num[b] = depth;

@@ -101,6 +101,10 @@ __device__ __forceinline__ int wave_min_i32(int v) {
     return wave_reduce_i(v, [](int a, int b) { return a < b ? a : b; });
 }
 
+__device__ __forceinline__ int wave_max_i32(int v) {
+    return wave_reduce_i(v, [](int a, int b) { return a > b ? a : b; });
+}
+
 // Block-wide max for blocks of up to 1024 threads; `red` holds >= 16 floats and
 // is not in use by the block when this is called.
 __device__ __forceinline__ float block_max(float v, float* red) {
