@@ -267,7 +267,8 @@ spec_status spec_fp8_gemm_silu_mul(const uint8_t* a, int64_t lda, const float* a
  *                       Zc = sum_{n in c} 2^(t_n - Mc), evaluated in fp32 in an
  *                            unspecified order (partial sums are rescaled as the
  *                            running maximum grows)
- *                       stats[m,c] = (Mc, Zc); an empty group is (-inf, 0)
+ *                       stats[m,c] = (Mc, Zc); an empty group, or one whose t_n are all
+ *                       -inf, is (-inf, 0)
  *     temperature == 0: stats[m,c] = (max_{n in c} z[m,n], lowest n attaining it as int32 bits);
  *                       an empty group is (-inf, INT32_MAX as int32 bits)
  *   so that max_c Mc and sum_c Zc * 2^(Mc - max) are the row's softmax maximum

@@ -36,9 +36,8 @@ __global__ __launch_bounds__(64) void logit_group_stats_kernel(GemmArgs g, int64
         mx = fmaxf(mx, z);
     }
     if (STATS == 1) {
-        const float zmax = wave_max(mx);
-        mx = zmax * g.c2;
-        if (zmax != -INFINITY)
+        mx = wave_max(mx) * g.c2;
+        if (mx != -INFINITY)
             for (int64_t e = e0 + lane; e < e1; e += 64)
                 s += __builtin_amdgcn_exp2f(bf16_to_f32(row[e]) * g.c2 - mx);
         s = wave_sum(s);

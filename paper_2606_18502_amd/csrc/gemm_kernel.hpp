@@ -611,7 +611,7 @@ __device__ __forceinline__ void store_staged(const GemmArgs& g, const v4f (&acc)
                         if (!EDGE || c0 + q * 8 + e < g.N) zmax = fmaxf(zmax, z_of(q, e));
                 const float M = zmax * g.c2;                 // = max t (c2 > 0; rounding is monotone)
                 float s = 0.0f;
-                if (zmax != -INFINITY) {
+                if (M != -INFINITY) {                        // (also where z * c2 overflows to -inf: no mass)
 #pragma unroll
                     for (int q = 0; q < kLaneChunks; ++q)
 #pragma unroll
