@@ -2,6 +2,8 @@
 // GEMM, and the workspace layout of the acceptance.  Plain C++ (no HIP), so
 // the argument checks and plans can also be built and exercised on a host
 // without a GPU.
+#include <utility>
+
 #include "kernels.hpp"
 #include "plan.hpp"
 
@@ -11,8 +13,8 @@ namespace {
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// Estimated time (us, up to a constant) of an M x N x K GEMM on tile kind
-// `kind` with K split `splits` ways: the K-steps of the busiest compute unit
+// Estimated time (us, up to a constant) of an M x N x K GEMM on a tile kind
+// with K split some ways: the K-steps of the busiest compute unit
 // (its workgroups share it, or follow each other where LDS holds no more), a
 // fixed cost per workgroup batch and its epilogue, the operand and output
 // bytes, and the split-K reduction.  The constants are a fit to timings of
@@ -24,43 +26,74 @@ inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // 13.0 us and the unsplit 64x64 tile 12.2; at 4096 x 3584, M = 160, 11.9 and 10.7;
 // at 3000 x 9984, M = 144, the 160x64 tile split in 5 takes 18.7 and 64x128 in 3
 // 17.7.
-double estimate_us(int64_t M, int64_t N, int64_t K, int kind, int splits) {
-    const TileShape& t = kTiles[kind];
-    const int64_t tiles = ((M + tile_bm(kind) - 1) / tile_bm(kind)) * ((N + tile_bn(kind) - 1) / tile_bn(kind));
-    const int64_t per_cu = (tiles * splits + 255) / 256;         // workgroups of the busiest of 256 compute units
-    const int64_t steps = (K / kGemmBK + splits - 1) / splits;
-    const int64_t resident = 160 / t.lds;
-    const double batches = (double)((per_cu + resident - 1) / resident);
-    const double blocks = t.wtm * t.wtn;                           // 16x16 blocks per wave
-    double us = t.step_us * (double)per_cu * (double)steps + batches * (1.61 + 0.102 * blocks) +
-                ((double)N * (double)K + (double)M * (double)K) / 10.1e6 + 0.119e-6 * 2.0 * (double)M * (double)N;
-    if (splits > 1) us += 0.7 + t.split_us + splits * (0.3 + 0.062 * blocks);
-    return us;
+//
+// Planning is on the host path of every call, so everything that depends on the
+// kind alone is a constant of an unrolled instance (no division by a variable):
+// 0.05-0.19 us a plan, 0.2-0.8 with a loop over the table.
+struct Best {
+    double us = -1.0;
+    int kind = kFarKind, splits = 1;
+};
+
+struct Shape {
+    int64_t M, N, ksteps;
+    int need;           // kHas* of the epilogue
+    bool may_split;
+    double traffic;     // the terms without kind or split
+    double out;
+    int64_t steps[9];   // K-steps of a workgroup by split
+};
+
+// The kind's split with the smallest estimate, if that is below the best so
+// far.  A split keeps at least 3 K-steps per workgroup and at most 640
+// workgroups (beyond both, partial tiles outweigh the gain).
+template <int KIND>
+inline void consider(const Shape& x, Best& best) {
+    constexpr TileShape t = kTiles[KIND];
+    constexpr int bm = tile_bm(KIND), bn = tile_bn(KIND), resident = 160 / t.lds;
+    constexpr double blocks = t.wtm * t.wtn;                           // 16x16 blocks per wave
+    if ((t.has & x.need) != x.need) return;
+    const int64_t tiles = ((x.M + bm - 1) / bm) * ((x.N + bn - 1) / bn);
+    const int max_splits = (t.has & kHasSplit) != 0 && x.may_split ? 8 : 1;
+    for (int s = 1; s <= max_splits; ++s) {
+        if (s > 1 && (x.ksteps < 3 * s || tiles * s > 640)) break;
+        const int64_t per_cu = (tiles * s + 255) / 256;                // workgroups of the busiest of 256 compute units
+        const double batches = (double)((per_cu + resident - 1) / resident);
+        double us = t.step_us * (double)per_cu * (double)x.steps[s] + batches * (1.61 + 0.102 * blocks) + x.traffic + x.out;
+        if (s > 1) us += 0.7 + t.split_us + s * (0.3 + 0.062 * blocks);
+        if (best.us < 0.0 || us < best.us) best = {us, KIND, s};
+    }
+}
+
+template <int... KIND>
+inline void consider_all(const Shape& x, Best& best, std::integer_sequence<int, KIND...>) {
+    (consider<KIND>(x, best), ...);
 }
 
 // The kind and split with the smallest estimate among those that have the
-// epilogue.  A split keeps at least 3 K-steps per workgroup and at most 640
-// workgroups (beyond both, partial tiles outweigh the gain).
+// epilogue.
 GemmPlan best_plan(int64_t M, int64_t N, int64_t K, int epilogue, bool may_split) {
-    const int need = epilogue == kEpiStats ? kHasStats : (epilogue == kEpiSilu ? kHasSilu : 0);
-    const int64_t ksteps = K / kGemmBK;
-    int kind = kFarKind, splits = 1;
-    double best = -1.0;
-    for (int k = 0; k < kTileKinds; ++k) {
-        if ((kTiles[k].has & need) != need) continue;
-        const int64_t tiles = ((M + tile_bm(k) - 1) / tile_bm(k)) * ((N + tile_bn(k) - 1) / tile_bn(k));
-        const bool can = may_split && epilogue == kEpiPlain && (kTiles[k].has & kHasSplit) != 0;
-        for (int s = 1; s <= (can ? 8 : 1); ++s) {
-            if (s > 1 && (ksteps / s < 3 || tiles * s > 640)) break;
-            const double us = estimate_us(M, N, K, k, s);
-            if (best < 0.0 || us < best) {
-                best = us;
-                kind = k;
-                splits = s;
-            }
-        }
+    Shape x{};
+    x.M = M;
+    x.N = N;
+    x.ksteps = K / kGemmBK;
+    x.need = epilogue == kEpiStats ? kHasStats : (epilogue == kEpiSilu ? kHasSilu : 0);
+    x.may_split = may_split && epilogue == kEpiPlain;
+    x.traffic = ((double)N * (double)K + (double)M * (double)K) / 10.1e6;
+    x.out = 0.119e-6 * 2.0 * (double)M * (double)N;
+    x.steps[1] = x.ksteps;
+    if (x.may_split) {
+        x.steps[2] = (x.ksteps + 1) / 2;
+        x.steps[3] = (x.ksteps + 2) / 3;
+        x.steps[4] = (x.ksteps + 3) / 4;
+        x.steps[5] = (x.ksteps + 4) / 5;
+        x.steps[6] = (x.ksteps + 5) / 6;
+        x.steps[7] = (x.ksteps + 6) / 7;
+        x.steps[8] = (x.ksteps + 7) / 8;
     }
-    return plan_gemm_as(M, N, K, kind, splits, epilogue);
+    Best best;
+    consider_all(x, best, std::make_integer_sequence<int, kTileKinds>{});
+    return plan_gemm_as(M, N, K, best.kind, best.splits, epilogue);
 }
 
 // A staggered K start pays where few M-tiles read many N-tiles of weights in

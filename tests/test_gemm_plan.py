@@ -8,6 +8,7 @@ import os
 import random
 import shutil
 import subprocess
+import time
 
 import pytest
 
@@ -35,6 +36,10 @@ def lib(tmp_path_factory):
     h = _lib.declare(ctypes.CDLL(out))
     h.test_plan_gemm.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.c_void_p]
     h.test_plan_gemm.restype = None
+    h.test_plan_search.argtypes = h.test_plan_gemm.argtypes
+    h.test_plan_search.restype = None
+    h.test_plan_many.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2
+    h.test_plan_many.restype = ctypes.c_int64
     return h
 
 
@@ -143,3 +148,28 @@ def test_a_workspace_is_required_where_k_is_split(lib):
         seen[required, p.splits > 1] += 1
     assert seen[True, True] and seen[True, False] and seen[False, True]
     assert plan(lib, 320, 4096, 4096).splits == 1 and lib.spec_fp8_gemm_workspace_bytes(320, 4096, 4096) > 0
+
+
+def test_the_unrolled_planner_finds_what_a_search_finds(lib):
+    out = (ctypes.c_int64 * 2)()
+    rng = random.Random(5)
+    for i in range(12000):
+        M = int(round(2 ** rng.uniform(0, 13)))
+        N, K = int(round(2 ** rng.uniform(3, 17.2))), 128 * int(round(2 ** rng.uniform(0, 7)))
+        for epilogue, may_split in ((PLAIN, True), (PLAIN, False), (STATS, True), (SILU, True)):
+            N8 = N if epilogue != SILU else N // 16 * 16 + 16
+            lib.test_plan_search(M, N8, K, epilogue, int(may_split), out)
+            p = plan(lib, M, N8, K, epilogue, may_split)
+            if p.m_tiles * p.n_tiles * 4 <= 4096 or out[1] == 1:         # (beyond the tickets no plan splits)
+                assert (p.kind, p.splits) == tuple(out), (M, N8, K, epilogue, may_split)
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 4096, 14336), (80, 4096, 14336), (320, 4096, 14336)])
+def test_planning_is_short(lib, M, N, K):
+    """A plan is on the host path of every call (about 3 us in all)."""
+    reps, best = 2000, 1e9
+    for _ in range(20):
+        t = time.perf_counter()
+        lib.test_plan_many(M, N, K, PLAIN, reps)
+        best = min(best, time.perf_counter() - t)
+    assert best / reps < 0.4e-6, best / reps
