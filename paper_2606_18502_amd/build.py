@@ -2,6 +2,9 @@
 
     python -m paper_2606_18502_amd.build [-v]
 
+(`python paper_2606_18502_amd/build.py` where torch is not installed: the
+library is a plain C ABI and is built without it.)
+
 Every HIP source is compiled with hipcc for gfx950 only, without packed-fp32
 instructions (-packed-fp32-ops) and without floating-point contraction
 (-ffp-contract=off keeps the documented rounding of every scale, exp and
@@ -49,13 +52,17 @@ def _hip_flags():
             "-Wall", "-Wno-unused-function", f"-I{os.path.join(ROOT, 'include')}"]
 
 
-def _torch_dir() -> str:
-    import torch
-    return os.path.dirname(torch.__file__)
+def _torch():
+    """The installed torch, or None: only the binding needs it."""
+    try:
+        import torch
+    except ImportError:
+        return None
+    return torch
 
 
-def _bind_compile(obj: str, torch_dir: str):
-    import torch
+def _bind_compile(obj: str, torch):
+    torch_dir = os.path.dirname(torch.__file__)
     inc = [os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
            os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
     return (["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
@@ -71,7 +78,8 @@ def _run(cmd):
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libspecfp8.so; returns the library path."""
+    """Compile every source and link libspecfp8.so, then the torch binding where
+    torch is installed; returns the library path."""
     os.makedirs(BUILD, exist_ok=True)
     cc = hipcc()
     jobs = []
@@ -86,20 +94,27 @@ def build(verbose: bool = False) -> str:
         jobs.append(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-I{os.path.join(ROOT, 'include')}",
                      "-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
-    torch_dir = _torch_dir()
+    torch = _torch()
     bind_obj = os.path.join(BUILD, BIND_SOURCE.replace(".", "_") + ".o")
-    jobs.append(_bind_compile(bind_obj, torch_dir))
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        bind = ex.submit(_run, _bind_compile(bind_obj, torch)) if torch else None
         for res in ex.map(_run, jobs):
             if verbose and (res.stdout or res.stderr):
                 print(res.stdout + res.stderr)
     tmp = LIB + ".tmp"
     _run([cc, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-Wl,-soname,libspecfp8.so", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    if bind is None:
+        print("torch is not installed: the torch binding is not built", file=sys.stderr)
+        return LIB
+    res = bind.result()
+    if verbose and (res.stdout or res.stderr):
+        print(res.stdout + res.stderr)
     # torch's own libraries are loaded by `import torch` before the binding is
     tmp = BIND + ".tmp"
     _run(["g++", "-shared", "-o", tmp, bind_obj, f"-L{HERE}", "-lspecfp8", "-Wl,-rpath,$ORIGIN",
-          f"-L{os.path.join(torch_dir, 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
+          f"-L{os.path.join(os.path.dirname(torch.__file__), 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu",
+          "-ltorch_python"])
     os.replace(tmp, BIND)
     return LIB
 
