@@ -155,9 +155,12 @@ bool truth(PyObject* o) {
     return r != 0;
 }
 
+// float(o) of Python, to fp32
 float number(PyObject* o) {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw python_error();
+    PyObject* f = PyNumber_Float(o);
+    if (!f) throw python_error();
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return (float)v;
 }
 

@@ -1,6 +1,8 @@
 """The native argument marshalling: what it refuses, and that outputs the
 caller gives come back as the same objects."""
 
+import fractions
+
 import pytest
 import torch
 
@@ -91,3 +93,19 @@ def test_an_unsplit_gemm_allocates_nothing_but_its_output(M, N, K):
     assert made() == before
     y = p.gemm(q, s, w, sw)
     assert made() == before + 1 and torch.equal(y, out)
+
+
+@pytest.mark.gpu
+def test_a_temperature_is_whatever_float_takes():
+    need_gpu()
+    d = dict(device="cuda")
+    z = torch.randn((2, 3, 512), **d).to(torch.bfloat16)
+    x, u = torch.zeros((2, 2), dtype=torch.int32, **d), torch.rand((2, 3), **d)
+    want = p.verify_accept(z, None, x, u, 0.75)
+    for T in ("0.75", fractions.Fraction(3, 4), torch.tensor(0.75), torch.full((1,), 0.75, **d)):
+        got = p.verify_accept(z, None, x, u, T)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    with pytest.raises(ValueError):
+        p.verify_accept(z, None, x, u, "warm")
+    with pytest.raises(TypeError):
+        p.verify_accept(z, None, x, u, None)
