@@ -144,9 +144,10 @@ __global__ __launch_bounds__(kQMaxThreads) void quantize_rows_kernel(
     }
 }
 
-// One given scale, one workgroup per row: a thread encodes its chunks one after
-// the other, or (PAIR) loads and unpacks its two chunks first.
-template <int IN_KIND, bool PAIR>
+// One given scale, one workgroup per row.  HOW 1: at most one chunk per thread;
+// 2: a thread's two chunks are unpacked before any is encoded; 0: its chunks
+// are encoded one after the other.
+template <int IN_KIND, int HOW>
 __global__ __launch_bounds__(kQMaxThreads) void quantize_static_rows_kernel(
     const uint16_t* __restrict__ x, int64_t cols, int64_t ld_x, const float* __restrict__ scale,
     uint8_t* __restrict__ q, int64_t ld_q) {
@@ -155,7 +156,11 @@ __global__ __launch_bounds__(kQMaxThreads) void quantize_static_rows_kernel(
     const uint16_t* xrow = x + row * ld_x;
     uint8_t* qrow = q + row * ld_q;
     const int t = threadIdx.x, nt = blockDim.x;
-    if constexpr (PAIR) {
+    if constexpr (HOW == 1) {
+        const RawChunk<IN_KIND> raw = load_raw<IN_KIND>(xrow, cols, min((int64_t)t, nchunks - 1));
+        const float inv = (float)(1.0 / (double)scale[0]);
+        if (t < nchunks) store_codes(qrow, t, chunk_values<IN_KIND>(raw), inv);
+    } else if constexpr (HOW == 2) {
         float v[2][8];
 #pragma unroll
         for (int j = 0; j < 2; ++j)
@@ -273,29 +278,39 @@ hipError_t launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld
 template <int IN_KIND>
 hipError_t launch_static(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld_x, const float* scale, uint8_t* q,
                          int64_t ld_q, hipStream_t stream) {
-    // Rows wider than one chunk per thread are split over workgroups until the
-    // chip is full several times over (SiLU-gated 14336 columns: 64 rows 4.0 ->
-    // 2.8 us, 320 rows 7.7 -> 6.5; 1005 rows 13.9 -> 14.3, so not beyond;
-    // [4000, 904] rows 3.8 -> 4.3).  Larger ones take one workgroup per row,
-    // which encodes chunk by chunk ([4096, 4096] 10.2 us; 10.6 when a thread's
-    // chunks are loaded first) but for the longest streams of plain rows
-    // ([4096, 14336] 28.9 -> 28.4 us the other way round).
+    // Rows wider than one chunk per thread are split over workgroups (one chunk
+    // per thread) while these are hardly more than the chip holds at once (2048:
+    // 8 per compute unit), for the SiLU-gated input a little beyond where every
+    // one is full, and wherever a row exceeds two chunks per thread of the
+    // largest workgroup.  Rows against split rows: 64 x 14336 3.1 -> 2.6 us,
+    // 400 x 9000 4.1 -> 3.9 and SiLU-gated 5.6 -> 5.4, SiLU-gated 320 x 14336
+    // 7.5 -> 7.0, 300 x 20000 5.9 -> 5.5; beyond the line 450 x 9000 4.2 -> 4.3
+    // and 6.2 -> 6.9.
+    // Otherwise one workgroup per row: a chunk per thread where that covers it
+    // (8192 x 2048 11.9 us, 12.4 with the code for more chunks), else chunk by
+    // chunk, but for long streams of plain rows (4096 x 14336 33.6 -> 32.9 us
+    // with both chunks first, 8192 x 4096 21.0 -> 20.4; 4096 x 4096 11.9 -> 12.1).
     const int64_t nchunks = cols / 8;
-    if (nchunks <= kQThreads || rows * nchunks > 600000) {
-        int threads = 64;
-        while (threads < kQMaxThreads && nchunks > (threads < kQThreads ? 1 : 2) * (int64_t)threads) threads *= 2;
-        const dim3 grid((unsigned)rows), block(threads);
-        if (IN_KIND == 0 && rows * nchunks > 5000000 && nchunks <= 2 * (int64_t)threads)
-            hipLaunchKernelGGL((quantize_static_rows_kernel<IN_KIND, true>), grid, block, 0, stream, x, cols, ld_x, scale,
-                               q, ld_q);
-        else
-            hipLaunchKernelGGL((quantize_static_rows_kernel<IN_KIND, false>), grid, block, 0, stream, x, cols, ld_x,
-                               scale, q, ld_q);
+    const int64_t per_row = (nchunks + kQThreads - 1) / kQThreads, blocks = rows * per_row;
+    const bool full = IN_KIND == 1 && nchunks % kQThreads == 0;
+    const bool split = nchunks > 2 * kQMaxThreads || (nchunks > kQThreads && blocks <= (full ? 2340 : 2100));
+    if (split && blocks <= 2147483647LL) {
+        hipLaunchKernelGGL(quantize_static_kernel<IN_KIND>, dim3((unsigned)blocks), dim3(kQThreads), 0, stream, x, cols,
+                           ld_x, scale, q, ld_q, (unsigned)per_row);
         return hipGetLastError();
     }
-    const unsigned per_row = (unsigned)((nchunks + kQThreads - 1) / kQThreads);
-    hipLaunchKernelGGL(quantize_static_kernel<IN_KIND>, dim3((unsigned)rows * per_row), dim3(kQThreads), 0, stream, x,
-                       cols, ld_x, scale, q, ld_q, per_row);
+    int threads = 64;
+    while (threads < kQMaxThreads && nchunks > (threads < kQThreads ? 1 : 2) * (int64_t)threads) threads *= 2;
+    const dim3 grid((unsigned)rows), block(threads);
+    if (nchunks <= threads)
+        hipLaunchKernelGGL((quantize_static_rows_kernel<IN_KIND, 1>), grid, block, 0, stream, x, cols, ld_x, scale, q,
+                           ld_q);
+    else if (IN_KIND == 0 && rows * nchunks > 3000000 && nchunks <= 2 * (int64_t)threads)
+        hipLaunchKernelGGL((quantize_static_rows_kernel<IN_KIND, 2>), grid, block, 0, stream, x, cols, ld_x, scale, q,
+                           ld_q);
+    else
+        hipLaunchKernelGGL((quantize_static_rows_kernel<IN_KIND, 0>), grid, block, 0, stream, x, cols, ld_x, scale, q,
+                           ld_q);
     return hipGetLastError();
 }
 

@@ -226,3 +226,25 @@ def test_row_splits_per_tensor_and_per_row(rows, cols, silu):
     st = np.float32(0.0123)
     q, _ = p.quantize(x, per_tensor_scale=dev_f32([st]), silu_mul=silu)
     np.testing.assert_array_equal(host(q)[pick], oq.quantize_per_tensor(v[pick], st))
+
+
+@pytest.mark.parametrize("rows,cols,silu", [
+    (3, 8, False), (70, 904, True), (70, 2040, False), (2600, 2048, True),       # a chunk per thread
+    (420, 8976, False), (421, 8976, False),                                       # 2100 workgroups of split rows, and beyond
+    (334, 14336, True), (335, 14336, True), (300, 14328, True), (301, 14328, True),   # 2338 full ones; 2100 with ragged ones
+    (3000, 8008, False), (2995, 8008, False),                                     # 3.0 M chunks: both first, one by one
+    (40, 16384, False), (700, 16384, True), (700, 16392, True),                   # two chunks per thread of 1024, one more
+])
+def test_per_tensor_launch_rules(rows, cols, silu):
+    """One given scale on both sides of every line of its launch rule."""
+    p = need_gpu()
+    say(f"quantize per-tensor rows={rows} cols={cols} silu={silu}")
+    xb = wl.linear_activations(rows, 2 * cols if silu else cols, seed=rows + cols)
+    x = dev_bf16(xb)
+    v = host_bf16_bits(p.silu_mul(x)) if silu else xb
+    out = torch.full((rows, cols + 16), 0x55, dtype=torch.uint8, device="cuda")
+    st = np.float32(0.0123)
+    p.quantize(x, per_tensor_scale=dev_f32([st]), silu_mul=silu, out=out[:, :cols])
+    assert torch.all(out[:, cols:] == 0x55)
+    pick = np.unique(np.linspace(0, rows - 1, min(rows, 64)).astype(int))
+    np.testing.assert_array_equal(host(out)[pick, :cols], oq.quantize_per_tensor(v[pick], st))
