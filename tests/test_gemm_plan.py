@@ -13,6 +13,7 @@ import time
 import pytest
 
 from paper_2606_18502_amd import _lib
+from tests import gemm_shapes
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_18502_amd", "csrc")
@@ -173,3 +174,30 @@ def test_planning_is_short(lib, M, N, K):
         lib.test_plan_many(M, N, K, PLAIN, reps)
         best = min(best, time.perf_counter() - t)
     assert best / reps < 0.4e-6, best / reps
+
+
+@pytest.mark.parametrize("epilogue,shapes", [
+    (SILU, gemm_shapes.SILU), (STATS, gemm_shapes.STATS), (PLAIN, gemm_shapes.SPLIT)], ids=["silu", "stats", "split"])
+def test_parity_shapes_reach_their_kernels(lib, epilogue, shapes):
+    for (M, N, K), want in shapes:
+        p = plan(lib, M, 2 * N if epilogue == SILU else N, K, epilogue)
+        assert (p.kind, p.splits, p.krot) == want, (M, N, K, p)
+
+
+def test_every_kernel_has_a_parity_shape(lib):
+    """Each kind and epilogue that a plan can reach, K split and staggered
+    starts among them, is named by a parity test."""
+    from tests.test_gpu_gemm_tiles import SHAPES
+    plain = {(p.kind, p.splits > 1) for p in (plan(lib, *s) for s in SHAPES)}
+    assert {k for k, split in plain if not split} == set(range(13))
+    assert {w[0] for _, w in gemm_shapes.SPLIT} | {k for k, split in plain if split} >= {3, 4, 5, 6, 7, 8, 9, 10, 11, 12}
+    named = {(e, w[0], w[2]) for e, t in ((SILU, gemm_shapes.SILU), (STATS, gemm_shapes.STATS)) for _, w in t}
+    rng = random.Random(9)
+    for _ in range(20000):
+        M = int(round(2 ** rng.uniform(0, 12)))
+        N, K = 16 * int(round(2 ** rng.uniform(1, 13))), 128 * int(round(2 ** rng.uniform(0, 7)))
+        for e in (SILU, STATS):
+            p = plan(lib, M, N, K, e)
+            assert (e, p.kind, p.krot) in named, (e, M, N, K, p)
+        p = plan(lib, M, N, K)
+        assert p.splits == 1 or p.kind >= 3, (M, N, K, p)

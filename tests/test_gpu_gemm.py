@@ -81,14 +81,14 @@ def _sample(n, count, seed):
 @pytest.mark.parametrize("M,N,K", [
     (8, 1024, 512),                     # C1
     (1, 16, 128), (17, 100, 256), (64, 64, 128),           # small tile, ragged
-    (80, 1040, 512), (100, 4096, 1024),                    # 80-row tile, split-K
-    (320, 640, 4096), (333, 272, 2048),                    # 320-row tile, split-K, ragged M
-    (300, 1000, 1024),                                     # 64x128 tile, ragged M and N, split-K
-    (700, 400, 512), (1024, 1024, 1024),                   # 256-row tile
+    (80, 1040, 512), (100, 4096, 1024),                    # M past one row of tiles, ragged N
+    (320, 640, 4096), (333, 272, 2048),                    # K split in 2; ragged M and N
+    (300, 1000, 1024),                                     # ragged M and N
+    (700, 400, 512), (1024, 1024, 1024),                   # many M-tiles
     (1300, 672, 256), (1777, 100, 128),                    # >= 8 M-tiles: grouped tile order, ragged group
-    (300, 60096, 256),                                     # 626 160x192 tiles (a wide N), ragged M
-    (250, 14336, 384), (161, 14336, 128),                  # 160x224 tiles: as many K-steps as stages, one K-step
-    (75, 12288, 384), (200, 2048, 9216),                   # 80x128 tiles: fewer K-steps than stages; K split, ragged M
+    (300, 60096, 256),                                     # a wide N, ragged M
+    (250, 14336, 384), (161, 14336, 128),                  # wide N: three K-steps, one K-step
+    (75, 12288, 384), (200, 2048, 9216),                   # fewer K-steps than stages, staggered; K split, ragged M
 ])
 def test_gemm_parity(M, N, K):
     p = need_gpu()
@@ -107,12 +107,11 @@ def test_gemm_parity(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K,out_f32,per_tensor,strided", [
-    # shapes the planner gives the long-prompt tiles whose fragments are
-    # refilled in place (fewer operand rows per CU than 160x224 tiles)
+    # shapes of the largest tiles (256x256, 160x384)
     (4096, 4096, 256, True, False, False),    # 256x256, one tile per CU; two K-steps: no steady-state loop
     (4000, 4000, 1024, True, False, True),    # 256x256, ragged M and N, strided operands and output
-    (2048, 7168, 512, False, False, False),   # 256x224, bf16 output
-    (2000, 7000, 512, True, True, True),      # 256x224, ragged, per-tensor activation scale, strided
+    (2048, 7168, 512, False, False, False),   # 160x384, bf16 output
+    (2000, 7000, 512, True, True, True),      # 160x384, ragged, per-tensor activation scale, strided
     (300, 128256, 256, True, False, True),    # 160x384 (an LM head's N at M <= 320), ragged M, strided
 ])
 def test_long_prompt_tiles(M, N, K, out_f32, per_tensor, strided):
@@ -149,8 +148,8 @@ def test_long_prompt_tiles(M, N, K, out_f32, per_tensor, strided):
 
 def test_long_prompt_operands_past_4gib():
     """A long-prompt shape whose activation rows lie more than 4 GiB apart in
-    total ((M - 1) * lda > 2^32): the 256-wide tiles address their operands
-    with 32-bit offsets, so the launcher must take the 160x224 kernel instead.
+    total ((M - 1) * lda > 2^32), those of one tile less: offsets are taken from
+    the tile's first row.
     Sampled rows against the oracle."""
     p = need_gpu()
     M, N, K = 2048, 14336, 256

@@ -11,6 +11,7 @@ import torch
 
 import workloads as wl
 from oracle import accept as oa, gemm as og, quantize as oq
+from tests import gemm_shapes
 from tests.gpu_util import dev_f32, dev_u8, host, host_bf16_bits, need_gpu, say
 from tests.test_gpu_gemm import TOL, _check_bound, _f32_to_bf16_bits, _sample
 
@@ -202,3 +203,14 @@ def test_far_rows_of_the_wide_lm_head_tile(T):
         assert torch.equal(sf.contiguous().view(torch.int32), sp.contiguous().view(torch.int32))
     else:
         torch.testing.assert_close(sf[..., 1], sp[..., 1], rtol=2e-5, atol=0)
+
+
+@pytest.mark.parametrize("M,V,K", [shape for shape, _ in gemm_shapes.STATS])
+@pytest.mark.parametrize("T", [0.7, 0.0])
+def test_statistics_of_every_tile(M, V, K, T):
+    test_statistics_of_the_stored_logits(M, V, K, T)
+
+
+@pytest.mark.parametrize("M,N,K", [shape for shape, _ in gemm_shapes.SPLIT])
+def test_split_tile_edges(M, N, K):
+    test_tile_edges(M, N, K)

@@ -71,13 +71,13 @@ def _lm_operands(p, M, V, K, seed, w_std):
 
 @pytest.mark.parametrize("M,V,K,T", [
     (8, 256, 512, 0.7),             # C1-sized
-    (80, 1000, 1024, 0.7),          # 80-row tile, ragged last column tile
-    (320, 13000, 512, 0.7),         # wide V: 160x192 tiles with a ragged last tile
+    (80, 1000, 1024, 0.7),          # ragged last tiles
+    (320, 13000, 512, 0.7),         # a wider V with a ragged last tile
     (333, 4104, 256, 1.3),          # M past 320, ragged M and V
-    (200, 1024, 4096, 0.7),         # long K: 160x128 tiles (never split here)
+    (200, 1024, 4096, 0.7),         # long K (never split here)
     (320, 6144, 1024, 0.0),         # greedy statistics
     (100, 4096, 512, 0.0),
-    (300, 32008, 256, 0.7),         # 160x384 tiles (fewer operand rows per CU than 160x224): ragged M,
+    (300, 32008, 256, 0.7),         # 160x384 tiles: ragged M,
     (300, 32008, 256, 0.0),         #   a last tile of 136 columns (its second wave's column group empty)
 ])
 def test_logit_stats_vs_oracle(M, V, K, T):
@@ -213,7 +213,7 @@ def test_lm_head_full_size():
 
     logits, stats = p.gemm_logit_stats(a_t, sa_t, w, sw, T)
     plain = p.gemm(a_t, sa_t, w, sw)
-    assert p.gemm_workspace_bytes(M, V, K) == 0        # no K split; both GEMMs walk K in order: identical bits
+    assert p.gemm_workspace_bytes(M, V, K) == 0        # no K split; both GEMMs walk K alike: identical bits
     assert torch.equal(logits.contiguous().view(torch.int16), plain.contiguous().view(torch.int16))
     zd = p.gemm(a_d, sa_d, w, sw)
 

@@ -16,10 +16,12 @@ fp32 summation order.
 
 import numpy as np
 import pytest
+import torch
 
 import workloads as wl
-from oracle import gemm as og, quantize as oq
-from tests.gpu_util import dev_bf16, host, host_bf16_bits, need_gpu, say
+from oracle import e4m3, gemm as og, quantize as oq
+from tests import gemm_shapes
+from tests.gpu_util import dev_bf16, dev_f32, dev_u8, host, host_bf16_bits, need_gpu, say
 
 pytestmark = pytest.mark.gpu
 
@@ -56,10 +58,10 @@ def _close(h, y_ref, I):
 
 
 @pytest.mark.parametrize("M,I,K", [
-    (8, 512, 512),          # 64-row tiles
-    (80, 1000, 1024),       # 80-row tiles, ragged last tile
+    (8, 512, 512),          # one partly filled row of tiles
+    (80, 1000, 1024),       # ragged last tiles
     (200, 2056, 512),       # ragged M and I
-    (333, 1024, 256),       # M past 320
+    (333, 1024, 256),       # several rows of tiles, the last ragged
 ])
 def test_silu_gemm_vs_oracle_and_unfused(M, I, K):
     p = need_gpu()
@@ -97,3 +99,29 @@ def test_silu_gemm_full_size_sampled():
     same = _close(h[np.ix_(rows, cols)], og.gemm(qa, sa_ref, qw, sw_ref), len(cols))
     say(f"silu gemm full size: equal to the oracle on {same:.5f} of sampled elements")
     assert same >= 0.9
+
+
+@pytest.mark.parametrize("M,I,K", [shape for shape, _ in gemm_shapes.SILU])
+def test_silu_tile_edges(M, I, K):
+    """Every tile kind with a SiLU epilogue at its edges: random codes scaled to
+    gate and up values of about 2, sampled outputs against the oracle, all of
+    them against the unfused path."""
+    p = need_gpu()
+    say(f"silu tile M={M} I={I} K={K}")
+    a, w = wl.fp8_code_bytes(M, K, seed=M + K), wl.fp8_code_bytes(2 * I, K, seed=I + K + 1)
+    rms = np.sqrt(np.mean(e4m3.decode(a[:1]).astype(np.float64) ** 2))
+    sa, sw = wl.uniform_scales(M, seed=M), wl.uniform_scales(2 * I, seed=I + 1)
+    sa = (sa / sa.mean() * 2.0 / (np.sqrt(K) * rms)).astype(np.float32)
+    sw = (sw / sw.mean() / rms).astype(np.float32)
+    args = (dev_u8(a), dev_f32(sa), dev_u8(w), dev_f32(sw))
+    out = torch.full((M, I + 8), -7.0, dtype=torch.bfloat16, device="cuda")
+    p.gemm_silu_mul(*args, out=out[:, :I])
+    assert torch.all(out[:, I:] == -7.0)
+    h = host_bf16_bits(out[:, :I])
+    rng = np.random.default_rng(6)
+    rows = np.unique(np.concatenate([[0, M - 1], rng.choice(M, min(M, 12), replace=False)]))
+    cols = np.unique(np.concatenate([[0, 7, 8, I - 1], rng.choice(I, 96, replace=False)]))
+    wrows = np.concatenate([cols, I + cols])
+    same = _close(h[np.ix_(rows, cols)], og.gemm(a[rows], sa[rows], w[wrows], sw[wrows]), len(cols))
+    assert same >= 0.9
+    assert np.mean(h == host_bf16_bits(p.silu_mul(p.gemm(*args)))) >= 0.995
