@@ -281,7 +281,8 @@ __device__ __forceinline__ void pin_frags(Frags<WTM, WTN>& f) {
 // registers in the loop follow those before and after it, and the compiler
 // rotated them by copies in every step of the 64x128 SiLU and the 160x64 and
 // 80x128 kernels, each copy waiting for the MFMA before it (SiLU-gated
-// M = 200, 2I = 7168, K = 8192: 33.4 us, 27.5 without).
+// M = 200, 2I = 7168, K = 8192: 33.4 us, 27.5 without).  The other small kernels
+// have no such copies and are left as they are.
 template <int WTM, int WTN>
 __device__ __forceinline__ void pin_acc(v4f (&acc)[WTN][WTM]) {
 #pragma unroll
@@ -937,9 +938,10 @@ __global__ __launch_bounds__(64 * kTiles[KIND].wm * kTiles[KIND].wn) void gemm_f
             step(yes, yes, full, p1);
         }
     } else {
-        pin_acc<WTM, WTN>(acc);
+        constexpr bool kPin = C::kMfma > 8 || (C::kMfma == 8 && EPI == 3);
+        if constexpr (kPin) pin_acc<WTM, WTN>(acc);
         for (; it + STAGES < nk; ++it) step(yes, yes, full, p0);
-        pin_acc<WTM, WTN>(acc);
+        if constexpr (kPin) pin_acc<WTM, WTN>(acc);
     }
     // the last STAGES steps (nk of them if there are fewer), no loads
     static_for<STAGES>([&](auto jc) {

@@ -20,8 +20,8 @@ inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // bytes, and the split-K reduction.  The constants are a fit to timings of
 // every kind and split (MI355X, cold weights, M from 1 to 4096).  What checks
 // them: over 80 linears of random and of the layer's shapes its choice takes
-// 0.3% longer than the fastest of all kinds and splits, 4.0% at most.  split_us
-// corrects two kinds whose splits the fit took for cheaper than they are: at
+// 0.3% longer than the fastest of all kinds and splits, 4.0% at most.  split_us and
+// more_us correct two kinds whose splits the fit took for cheaper than they are: at
 // 6144 x 4096, M = 80, the 80x64 tile split in 2 takes 13.0 us and the unsplit
 // 64x64 tile 12.2; at 4096 x 3584, M = 160, 11.9 and 10.7; at 3000 x 9984, M =
 // 144, the 160x64 tile split in 5 takes 18.7 and 64x128 in 3 17.7.
@@ -59,7 +59,7 @@ inline void consider(const Shape& x, Best& best) {
         const int64_t per_cu = (tiles * s + 255) / 256;                // workgroups of the busiest of 256 compute units
         const double batches = (double)((per_cu + resident - 1) / resident);
         double us = t.step_us * (double)per_cu * (double)x.steps[s] + batches * (1.61 + 0.102 * blocks) + x.traffic + x.out;
-        if (s > 1) us += 0.7 + t.split_us + s * (0.3 + 0.062 * blocks);
+        if (s > 1) us += 0.7 + t.split_us + (s - 2) * t.more_us + s * (0.3 + 0.062 * blocks);
         if (best.us < 0.0 || us < best.us) best = {us, KIND, s};
     }
 }

@@ -16,12 +16,12 @@ namespace specfp8 {
 // MFMA late8/8 of the step.  staged: the plain bf16 output leaves through LDS
 // (statistics epilogues always do).  has: the kernels a kind has beside the
 // plain one (each is compiled separately).  step_us: the time of one K-step of
-// a workgroup alone on a compute unit, split_us: what a K split costs beyond
-// the estimate's common term, and lds the KiB a workgroup holds, for the
-// planner's estimate (plan.cpp).
+// a workgroup alone on a compute unit, split_us and more_us: what a K split in
+// two and each further split cost beyond the estimate's common term, and lds the
+// KiB a workgroup holds, for the planner's estimate (plan.cpp).
 struct TileShape {
     int wtm, wtn, wm, wn, stages, lspan8, late8, t1, staged, has;
-    double step_us, split_us;
+    double step_us, split_us, more_us;
     int lds;
 };
 constexpr int kHasSplit = 1, kHasStats = 2, kHasSilu = 4;
@@ -41,19 +41,19 @@ constexpr int kHasSplit = 1, kHasStats = 2, kHasSilu = 4;
 // 11    64 x 64   2x2 (32x32)        4
 // 12    32 x 64   1x4 (32x16)        4        (a 16 x 64 tile was no faster at any M)
 constexpr TileShape kTiles[] = {
-    {8, 8, 2, 2, 2, 6, 3, 5, 1, kHasStats, 0.991, 0, 134},
-    {5, 12, 2, 2, 2, 6, 3, 4, 1, kHasStats, 1.034, 0, 139},
-    {5, 7, 2, 2, 3, 6, 0, 3, 1, kHasSilu, 0.643, 0, 146},
-    {4, 8, 2, 2, 3, 6, 0, 3, 1, kHasSplit | kHasStats | kHasSilu, 0.668, 0, 146},
-    {8, 4, 2, 2, 3, 6, 0, 3, 0, kHasSplit, 0.659, 0, 146},
-    {5, 4, 2, 2, 4, 6, 0, 3, 0, kHasSplit, 0.479, 0, 146},
-    {4, 4, 2, 2, 4, 6, 0, 3, 0, kHasSplit | kHasStats | kHasSilu, 0.433, 0, 129},
-    {5, 2, 2, 2, 4, 8, 0, 0, 0, kHasSplit, 0.362, 0.2, 113},
-    {2, 4, 2, 2, 4, 8, 0, 0, 0, kHasSplit | kHasStats | kHasSilu, 0.319, 0, 97},
-    {5, 2, 1, 4, 3, 8, 0, 0, 0, kHasSplit | kHasSilu, 0.390, 0, 79},
-    {5, 1, 1, 4, 4, 8, 0, 0, 0, kHasSplit, 0.261, 0.5, 73},
-    {2, 2, 2, 2, 4, 8, 0, 0, 0, kHasSplit | kHasSilu, 0.207, 0, 65},
-    {2, 1, 1, 4, 4, 8, 0, 0, 0, kHasSplit, 0.169, 0, 49},
+    {8, 8, 2, 2, 2, 6, 3, 5, 1, kHasStats, 0.991, 0, 0, 134},
+    {5, 12, 2, 2, 2, 6, 3, 4, 1, kHasStats, 1.034, 0, 0, 139},
+    {5, 7, 2, 2, 3, 6, 0, 3, 1, kHasSilu, 0.643, 0, 0, 146},
+    {4, 8, 2, 2, 3, 6, 0, 3, 1, kHasSplit | kHasStats | kHasSilu, 0.668, 0, 0, 146},
+    {8, 4, 2, 2, 3, 6, 0, 3, 0, kHasSplit, 0.659, 0, 0, 146},
+    {5, 4, 2, 2, 4, 6, 0, 3, 0, kHasSplit, 0.479, 0, 0, 146},
+    {4, 4, 2, 2, 4, 6, 0, 3, 0, kHasSplit | kHasStats | kHasSilu, 0.433, 0, 0, 129},
+    {5, 2, 2, 2, 4, 8, 0, 0, 0, kHasSplit, 0.362, 0, 0.1, 113},
+    {2, 4, 2, 2, 4, 8, 0, 0, 0, kHasSplit | kHasStats | kHasSilu, 0.319, 0, 0, 97},
+    {5, 2, 1, 4, 3, 8, 0, 0, 0, kHasSplit | kHasSilu, 0.390, 0, 0, 79},
+    {5, 1, 1, 4, 4, 8, 0, 0, 0, kHasSplit, 0.261, 0.5, 0, 73},
+    {2, 2, 2, 2, 4, 8, 0, 0, 0, kHasSplit | kHasSilu, 0.207, 0, 0, 65},
+    {2, 1, 1, 4, 4, 8, 0, 0, 0, kHasSplit, 0.169, 0, 0, 49},
 };
 constexpr int kTileKinds = sizeof(kTiles) / sizeof(kTiles[0]);
 constexpr int kLmHeadKind = 1;

@@ -39,7 +39,7 @@ void test_plan_search(int64_t M, int64_t N, int64_t K, int epilogue, int may_spl
                         (double)((per_cu + resident - 1) / resident) * (1.61 + 0.102 * blocks) +
                         ((double)N * (double)K + (double)M * (double)K) / 10.1e6 +
                         0.119e-6 * 2.0 * (double)M * (double)N;
-            if (s > 1) us += 0.7 + t.split_us + s * (0.3 + 0.062 * blocks);
+            if (s > 1) us += 0.7 + t.split_us + (s - 2) * t.more_us + s * (0.3 + 0.062 * blocks);
             if (best < 0.0 || us < best) {
                 best = us;
                 out[0] = k;
