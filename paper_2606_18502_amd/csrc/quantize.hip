@@ -294,7 +294,7 @@ hipError_t launch_static(const uint16_t* x, int64_t rows, int64_t cols, int64_t 
     const int64_t per_row = (nchunks + kQThreads - 1) / kQThreads, blocks = rows * per_row;
     const bool full = IN_KIND == 1 && nchunks % kQThreads == 0;
     const bool split = nchunks > 2 * kQMaxThreads || (nchunks > kQThreads && blocks <= (full ? 2340 : 2100));
-    if (split && blocks <= 2147483647LL) {
+    if (split && blocks * kQThreads <= 4294967295LL) {      // (a grid's threads are counted in 32 bits)
         hipLaunchKernelGGL(quantize_static_kernel<IN_KIND>, dim3((unsigned)blocks), dim3(kQThreads), 0, stream, x, cols,
                            ld_x, scale, q, ld_q, (unsigned)per_row);
         return hipGetLastError();
