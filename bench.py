@@ -915,7 +915,7 @@ def profile_gemm_c5(torch, p, wl, rounds=5, copies=3):
     `rounds` rounds of the C5 up (M = 4096, 4096 -> 14336) and down
     (14336 -> 4096) projections over `copies` weight copies each (6 x 58.7 MB
     exceed the 256 MB Infinity Cache, so every launch finds its weights cold).
-    The two shapes run kernels of their own (256x224 and 256x256 tiles)."""
+    Both run the 256x256 tile."""
     c5 = wl.CONFIGS["C5"]
     M = c5["M"]
     shapes = {"up": (c5["N1"], c5["K1"]), "down": (c5["K1"], c5["N1"])}

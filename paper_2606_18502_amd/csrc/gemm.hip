@@ -21,11 +21,10 @@ extern template hipError_t launch_gemm_kind<12>(int, const GemmArgs&, hipStream_
 namespace {
 
 // Statistics of stored logits per column group (epilogues 1 and 2's entries),
-// for the path whose GEMM kernel has no statistics epilogue: one wave per
-// (row, group), lanes strided over the group's columns.
+// for the path whose GEMM kernel has no statistics epilogue: waves strided over
+// the (row, group) pairs, lanes over a group's columns.
 template <int STATS>
-__global__ __launch_bounds__(64) void logit_group_stats_kernel(GemmArgs g, int64_t groups, int64_t group_cols) {
-    const int64_t m = blockIdx.x / groups, c = blockIdx.x % groups;
+__device__ __forceinline__ void logit_group_stats(const GemmArgs& g, int64_t m, int64_t c, int64_t group_cols) {
     const int lane = threadIdx.x;
     const int64_t e0 = c * group_cols, e1 = min(e0 + group_cols, (int64_t)g.N);
     const uint16_t* row = reinterpret_cast<const uint16_t*>(g.y) + m * g.ldy;
@@ -51,6 +50,13 @@ __global__ __launch_bounds__(64) void logit_group_stats_kernel(GemmArgs g, int64
     }
     if (lane == 0) g.stats[m * g.ld_stats + c] = make_float2(mx, s);
 }
+
+template <int STATS>
+__global__ __launch_bounds__(64) void logit_group_stats_kernel(GemmArgs g, int64_t groups, int64_t group_cols) {
+    for (int64_t i = blockIdx.x; i < g.M * groups; i += gridDim.x)
+        logit_group_stats<STATS>(g, i / groups, i % groups, group_cols);
+}
+constexpr int64_t kGroupStatsWaves = 256 * 32;   // what the chip holds
 
 }  // namespace
 
@@ -106,8 +112,8 @@ hipError_t launch_gemm(const GemmPlan& p, const uint8_t* a, int64_t lda, const f
     hipError_t e = launch_gemm_far(epi == 3 ? 3 : 0, g, stream);
     if (e != hipSuccess || stats_mode == 0) return e;
     const int64_t cols = tile_bn(p.kind) / kTiles[p.kind].wn;
-    if ((int64_t)M * p.stat_groups > 2147483647LL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(M * p.stat_groups));
+    const int64_t items = M * p.stat_groups;
+    const dim3 grid((unsigned)(items < kGroupStatsWaves ? items : kGroupStatsWaves));
     if (stats_mode == 1)
         hipLaunchKernelGGL(logit_group_stats_kernel<1>, grid, dim3(64), 0, stream, g, p.stat_groups, cols);
     else hipLaunchKernelGGL(logit_group_stats_kernel<2>, grid, dim3(64), 0, stream, g, p.stat_groups, cols);
