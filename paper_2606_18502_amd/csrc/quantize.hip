@@ -6,8 +6,9 @@
 // so every wave reads 1 KiB contiguous per instruction), all issued before any
 // is used, and kept in registers as packed bf16; the block reduces max|v| (wave
 // shuffles, then LDS across waves), derives the scale, and encodes the
-// registers it already holds ([4096, 14336]: 29.6 us, 5.9 TB/s; 31.4 with the
-// loads issued one by one into fp32 registers).  HBM traffic
+// registers it already holds ([2048, 14336] 18.7 us, [4096, 14336] 35.3, timed in
+// turn over rotated inputs; 20.3 and 35.8 with the loads issued one by one into
+// fp32 registers).  HBM traffic
 // is therefore the algorithmic 2 bytes in + 1 byte out per element (4 + 1 for
 // the SiLU-gated input) plus 4 bytes of scale per row.  Rows wider than
 // 65536 elements take a second pass that re-reads the row.
